@@ -108,7 +108,8 @@ __host__ __device__ __forceinline__ cd tmul(cd a)
 }
 
 // In-place radix-2 transform of length L (SIGN -1 forward, +1 inverse), natural order
-// in and out.
+// in and out.  A butterfly (a + w b, a - w b) with a twiddle that needs multiplications
+// is six fused operations: s = a + w b in four, then 2 a - s.
 template <int L, int SIGN>
 __host__ __device__ __forceinline__ void transform(cd (&v)[L])
 {
@@ -130,50 +131,19 @@ __host__ __device__ __forceinline__ void transform(cd (&v)[L])
             constexpr int base = decltype(bc)::value * len;
             sfor<0, half>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
-                const cd a = v[base + j];
-                const cd b = tmul<j, len, SIGN>(v[base + j + half]);
-                v[base + j] = cadd(a, b);
-                v[base + j + half] = csub(a, b);
+                const cd a = v[base + j], b = v[base + j + half];
+                if constexpr (j == 0 || 4 * j == len) {
+                    const cd t = tmul<j, len, SIGN>(b);
+                    v[base + j] = cadd(a, t);
+                    v[base + j + half] = csub(a, t);
+                } else {
+                    constexpr cd w = twiddle(j, len, SIGN);
+                    const cd s = {fma(w.re, b.re, fma(-w.im, b.im, a.re)), fma(w.re, b.im, fma(w.im, b.re, a.im))};
+                    v[base + j] = s;
+                    v[base + j + half] = cd{fma(2.0, a.re, -s.re), fma(2.0, a.im, -s.im)};
+                }
             });
         });
-    });
-}
-
-// Forward transform of length 2H whose inputs H..2H-1 are zero: from the H given
-// values, out[0..2H) (even outputs = transform of x, odd = transform of x_j w^j).
-template <int H>
-__host__ __device__ __forceinline__ void fft_fwd_padded(const cd (&x)[H], cd (&out)[2 * H])
-{
-    cd e[H], o[H];
-    sfor<0, H>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        e[j] = x[j];
-        o[j] = tmul<j, 2 * H, -1>(x[j]);
-    });
-    transform<H, -1>(e);
-    transform<H, -1>(o);
-    sfor<0, H>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        out[2 * m] = e[m];
-        out[2 * m + 1] = o[m];
-    });
-}
-
-// Inverse transform of length 2H keeping only outputs 0..H-1.
-template <int H>
-__host__ __device__ __forceinline__ void fft_inv_half(const cd (&X)[2 * H], cd (&out)[H])
-{
-    cd e[H], o[H];
-    sfor<0, H>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        e[m] = X[2 * m];
-        o[m] = X[2 * m + 1];
-    });
-    transform<H, +1>(e);
-    transform<H, +1>(o);
-    sfor<0, H>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        out[j] = cadd(e[j], tmul<j, 2 * H, +1>(o[j]));
     });
 }
 

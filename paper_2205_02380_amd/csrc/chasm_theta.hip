@@ -12,8 +12,7 @@
 #include <vector>
 
 #include "../../include/chasm_theta.h"
-#include "chasm_theta.hpp"
-#include "chasm_theta_big.hpp"
+#include "chasm_theta_launch.hpp"
 
 namespace chasm {
 
@@ -159,85 +158,12 @@ static void tensor_partial(const int nk[3], const std::vector<double>& T, std::v
             }
 }
 
-// ---------------------------------------------------------------------------
-// Compiled kernels: (storage type, nk) -> chunk count R and block size of the one-block
-// form (nk 8, 16), and the staged form over batches of x-points (nk 16, 32, 64).
-using BigFn = hipError_t (*)(void* fx, const double* kt, const ThetaArgs& a, fft::cd* W, double* acc,
-                             long long total, long long X, hipStream_t s);
-
-struct ThetaKernels {
-    int dtype, nk;
-    hipError_t (*theta)(void* fx, const double* kt, const ThetaArgs& a, long long total, hipStream_t s);
-    hipError_t (*transpose)(const void* in, void* out, long long rows, long long cols, int batch, hipStream_t s);
-    BigFn big;                 // staged form (nullptr: none)
-};
-
-template <typename K>
-static long long resident(K k, int threads)
-{
-    int dev = 0, ncu = 0, per = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, threads, 0) != hipSuccess) return 0;
-    return (long long)ncu * (per > 0 ? per : 1);
-}
-
-template <typename T, int NK, int R, int NT>
-static hipError_t launch_theta(void* fx, const double* kt, const ThetaArgs& a, long long total, hipStream_t s)
-{
-    auto k = k_theta<T, NK, R, NT>;
-    const long long res = resident(k, NT);
-    const unsigned grid = (unsigned)(res > 0 && res < total ? res : total);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(NT), 0, s, static_cast<T*>(fx), kt, a, total);
-    return hipGetLastError();
-}
-
-// Staged form: x-points in batches of X; per batch and nucleus the three stages.
-template <typename T, int NK>
-static hipError_t launch_big(void* fx, const double* kt, const ThetaArgs& a, fft::cd* W, double* acc,
-                             long long total, long long X, hipStream_t s)
-{
-    using B = BigShape<NK>;
-    for (long long x0 = 0; x0 < total; x0 += X) {
-        const long long nb = total - x0 < X ? total - x0 : X;
-        for (int nu = 0; nu < a.nnuc; ++nu) {
-            hipLaunchKernelGGL((k_thA<T, NK>), dim3((unsigned)(nb * B::BPX)), dim3(64), 0, s,
-                               static_cast<const T*>(fx), W, a, x0, nu);
-            hipLaunchKernelGGL((k_thBCD<NK>), dim3((unsigned)(nb * B::P)), dim3(B::NTB), 0, s, W, kt);
-            hipLaunchKernelGGL((k_thE<T, NK>), dim3((unsigned)(nb * B::BPX)), dim3(64), 0, s, W, acc,
-                               static_cast<T*>(fx), a, x0, nu, nu == 0 ? 1 : 0, nu == a.nnuc - 1 ? 1 : 0);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-    }
-    return hipSuccess;
-}
-
-template <typename T>
-static hipError_t launch_transpose(const void* in, void* out, long long rows, long long cols, int batch, hipStream_t s)
-{
-    const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64), (unsigned)batch);
-    hipLaunchKernelGGL(k_transpose<T>, grid, dim3(256), 0, s, static_cast<const T*>(in), static_cast<T*>(out), rows,
-                       cols);
-    return hipGetLastError();
-}
-
-static const ThetaKernels kThetaKernels[] = {
-    {CHASM_F32, 8, launch_theta<float, 8, 1, 256>, launch_transpose<float>, nullptr},
-    {CHASM_F64, 8, launch_theta<double, 8, 1, 256>, launch_transpose<double>, nullptr},
-    {CHASM_F32, 16, launch_theta<float, 16, 4, 256>, launch_transpose<float>, launch_big<float, 16>},
-    {CHASM_F64, 16, launch_theta<double, 16, 4, 256>, launch_transpose<double>, launch_big<double, 16>},
-    {CHASM_F32, 32, nullptr, launch_transpose<float>, launch_big<float, 32>},
-    {CHASM_F64, 32, nullptr, launch_transpose<double>, launch_big<double, 32>},
-    {CHASM_F32, 64, nullptr, launch_transpose<float>, launch_big<float, 64>},
-    {CHASM_F64, 64, nullptr, launch_transpose<double>, launch_big<double, 64>},
-};
-
+// The kernels of (dtype, nk), or nullptr.
 static const ThetaKernels* find_theta(int dtype, int nk)
 {
-    for (const ThetaKernels& k : kThetaKernels)
-        if (k.dtype == dtype && k.nk == nk) return &k;
-    return nullptr;
+    const ThetaKernels* k = nk == 8 ? theta_kernels_8() : nk == 16 ? theta_kernels_16() : nk == 32 ? theta_kernels_32()
+                            : nk == 64 ? theta_kernels_64() : nullptr;
+    return k ? &k[dtype == CHASM_F64 ? 1 : 0] : nullptr;
 }
 
 // Staged form: x-points per batch (intermediate W of X * 2 nk^3 complex values, at most
@@ -264,6 +190,7 @@ struct chasm_theta_s {
     hipStream_t stream = nullptr;
     const ThetaKernels* ks = nullptr;
     double* kt = nullptr;               // kernel transformed along k1, k2 (tensor_partial)
+    fft::cd* et = nullptr;              // modulation factors of the grid's nodes (k_theta_mod)
     void* ws = nullptr;
     bool big = false;                   // staged form
     long long X = 0;                    // x-points per batch of the staged form
@@ -331,6 +258,8 @@ chasm_status chasm_theta_workspace_bytes(const chasm_theta_desc* desc, size_t* b
     const size_t pts = (size_t)desc->nx[0] * desc->nx[1] * desc->nx[2] * desc->nk[0] * desc->nk[1] * desc->nk[2];
     const size_t P3 = (size_t)8 * desc->nk[0] * desc->nk[1] * desc->nk[2];
     *bytes = pts * desc->nbatch * es + P3 * sizeof(double) + 512;
+    const size_t nrow = (size_t)desc->nx[0] + desc->nx[1] + desc->nx[2];
+    *bytes += (2 + (size_t)desc->nnuc * nrow) * desc->nk[0] * sizeof(fft::cd) + 256;
     if (use_big(desc, ks)) {
         const long long nk = desc->nk[0];
         const long long X = big_batch((int)nk, (long long)desc->nx[0] * desc->nx[1] * desc->nx[2] * desc->nbatch);
@@ -403,8 +332,6 @@ chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, 
         if (desc->nnuc > 1 && hipMalloc((void**)&h->acc, (size_t)h->X * nkk * nkk * nkk * sizeof(double)) != hipSuccess)
             return bail(CHASM_ENOMEM, "hipMalloc(staged accumulator) failed");
     }
-    if (hipStreamSynchronize(h->stream) != hipSuccess) return bail(CHASM_EDEVICE, "stream synchronize failed");
-
     ThetaArgs& a = h->args;
     a.npts = h->npts;
     a.nnuc = desc->nnuc;
@@ -419,6 +346,10 @@ chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, 
         for (int d = 0; d < 3; ++d) a.xa[i][d] = desc->x_nuc[i][d];
         a.wgt[i] = desc->z_nuc[i] * (2.0 / (M_PI * M_PI)) / P3;     // z_a 4/c_{3,1}, c_{3,1} = 2 pi^2; 1/P^3 of the inverse
     }
+    if (hipMalloc((void**)&h->et, (size_t)mod_rows(a) * nk[0] * sizeof(fft::cd)) != hipSuccess)
+        return bail(CHASM_ENOMEM, "hipMalloc(modulation table) failed");
+    if (ks->mod(h->et, a, h->stream) != hipSuccess) return bail(CHASM_EDEVICE, "modulation table launch failed");
+    if (hipStreamSynchronize(h->stream) != hipSuccess) return bail(CHASM_EDEVICE, "stream synchronize failed");
     *out = h;
     return CHASM_OK;
 }
@@ -430,8 +361,8 @@ chasm_status chasm_theta_apply(chasm_theta_t h, const void* f_dev, void* out_dev
     const int nb = h->desc.nbatch;
     hipError_t e = h->ks->transpose(f_dev, h->ws, h->nkp, h->npts, nb, h->stream);
     if (e == hipSuccess)
-        e = h->big ? h->ks->big(h->ws, h->kt, h->args, h->W, h->acc, h->npts * nb, h->X, h->stream)
-                   : h->ks->theta(h->ws, h->kt, h->args, h->npts * nb, h->stream);
+        e = h->big ? h->ks->big(h->ws, h->kt, h->et, h->args, h->W, h->acc, h->npts * nb, h->X, h->stream)
+                   : h->ks->theta(h->ws, h->kt, h->et, h->args, h->npts * nb, h->stream);
     if (e == hipSuccess) e = h->ks->transpose(h->ws, out_dev, h->npts, h->nkp, nb, h->stream);
     if (e != hipSuccess) {
         h->poisoned = true;
@@ -445,6 +376,7 @@ chasm_status chasm_theta_destroy(chasm_theta_t h)
     if (!h) return CHASM_OK;
     if (h->stream) hipStreamSynchronize(h->stream);
     if (h->kt) hipFree(h->kt);
+    if (h->et) hipFree(h->et);
     if (h->ws) hipFree(h->ws);
     if (h->W) hipFree(h->W);
     if (h->acc) hipFree(h->acc);

@@ -1,7 +1,7 @@
 // chasm_theta_big.hpp -- the truncated-kernel evaluation of Theta_V (Sec. 4, eq. 4.6
 // with the tensor of eq. 4.9) for k-grids whose per-x-point intermediate does not fit
 // in one CU (N_k = 32 and 64; also built for 16 to check it against the one-block form
-// of chasm_theta.hpp).  Same mathematics as k_theta:
+// of chasm_theta_plane.hpp).  Same mathematics as k_theta:
 //   Theta(x, k_p) = sum_a w_a Im( e^{i phi_a.p} [circular convolution of period
 //                   P = 2 N_k of T with the zero-padded e^{-i phi_a.p'} f_p'](p) ),
 // evaluated in three stages over a batch of x-points, with a complex FP64
@@ -15,13 +15,15 @@
 // Every P-point transform of a zero-padded line, and every inverse restricted to the
 // first N_k outputs, is split by residue: output (input) index S f + h, f < 32,
 // h < S = P / 32, is a 32-point transform of the twiddled line folded modulo 32, so
-// each work item holds 32 complex values in registers.  The field is in x-major order
-// [b][x][k3][k2][k1], as for k_theta.
+// each work item of A and E holds 32 complex values in registers.  The field is in x-major
+// order [b][x][k3][k2][k1], as for k_theta.  The modulations are per-axis factors of the
+// handle's table: k1 and k3 in A and E (one product table per block), k2 in k_thBCD.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include "chasm_fft.hpp"
 #include "chasm_theta.hpp"
+#include "chasm_theta_plane.hpp"
 
 namespace chasm {
 
@@ -31,90 +33,132 @@ struct BigShape {
     static constexpr int L = 32;              // transform length of a work item
     static constexpr int S = P / L;           // residues
     static constexpr int RS = NK + 1;         // padded LDS row (complex)
-    static constexpr int LPB = 64;            // k-lines per block in A and E
-    static constexpr int BPX = NK * NK / LPB; // blocks per x-point in A and E
+    static constexpr int LA = 256;            // k1 lines (threads) per block in A
+    static constexpr int LE = NK <= 32 ? 256 : 64;          // and in E
     static constexpr int NTB = 2 * NK > 64 ? 2 * NK : 64;   // threads of k_thBCD
-    static_assert(P % L == 0 && NK * NK % LPB == 0, "shape");
+    static_assert(P % L == 0 && NK * NK % LA == 0 && LE % NK == 0, "shape");
 };
 
-// Coordinates of global x-point xp (batch members stacked) and the modulation table
-// E[d][k] = e^{-i phi_d k}, phi_d = 2 (x_d - x_a,d) hk_d, of nucleus nu.
-template <int NK>
-__device__ __forceinline__ void big_modulation(const ThetaArgs& a, long long xp, int nu, fft::cd (*E)[NK])
+// The factors that A and E apply along k1 on the block's KR rows k3 = r0 .. r0 + KR - 1:
+// e02[h][kr][j] = e^{-i phi_1 j} w^{h j} e^{-i phi_3 k3} (the k2 factor rides on the
+// twiddles of B and D).
+template <int NK, int KR>
+__device__ __forceinline__ void big_factors(fft::cd (*e02)[KR][NK], const fft::cd* et, const ModRows& e, int r0)
 {
-    const long long loc = xp % a.npts;
-    const int i1 = (int)(loc % a.nx[0]);
-    const int i2 = (int)((loc / a.nx[0]) % a.nx[1]);
-    const int i3 = (int)(loc / ((long long)a.nx[0] * a.nx[1]));
-    const double xc[3] = {a.x_lo[0] + i1 * a.hx[0], a.x_lo[1] + i2 * a.hx[1], a.x_lo[2] + i3 * a.hx[2]};
-    for (int t = threadIdx.x; t < 3 * NK; t += blockDim.x) {
-        const int d = t / NK, k = t % NK;
-        const double ph = 2.0 * (xc[d] - a.xa[nu][d]) * a.hk[d] * k;
-        double s, c;
-        sincos(ph, &s, &c);
-        E[d][k] = fft::cd{c, -s};
+    using namespace fft;
+    constexpr int S = BigShape<NK>::S;
+    for (int t = threadIdx.x; t < S * KR * NK; t += blockDim.x) {
+        const int j = t % NK, kr = (t / NK) % KR, h = t / (NK * KR);
+        e02[h][kr][j] = cmul(cmul(e.e1[j], et[(h * j) % (2 * NK)]), e.e3[r0 + kr]);
     }
 }
 
-// ---- A: k1 forward.  Block = 64 k1 lines of one x-point, a thread per line.
+// ---- A: k1 forward.  Block = 256 k1 lines of one x-point, a thread per line and one
+// residue h (outputs xi1 = S f + h) at a time: 32 complex values in registers.
 template <typename T, int NK>
-__global__ __launch_bounds__(64) void k_thA(const T* __restrict__ fx, fft::cd* __restrict__ W, const ThetaArgs a,
-                                            long long x0, int nu)
+__global__ __launch_bounds__(BigShape<NK>::LA, 2) void k_thA(const T* __restrict__ fx, fft::cd* __restrict__ W,
+                                                            const fft::cd* __restrict__ et, const ThetaArgs a,
+                                                            long long x0, int nu)
 {
     using namespace fft;
     using B = BigShape<NK>;
-    constexpr int P = B::P, S = B::S;
-    __shared__ cd E[3][NK];
-    const long long xl = blockIdx.x / B::BPX;
-    const int la = (int)(blockIdx.x % B::BPX) * B::LPB + threadIdx.x;   // k3 * NK + k2
-    const int k2 = la % NK, k3 = la / NK;
-    big_modulation<NK>(a, x0 + xl, nu, E);
+    constexpr int P = B::P, S = B::S, KR = B::LA / NK, BPX = NK * NK / B::LA;
+    __shared__ cd E02[S][KR][NK];
+    const long long xl = blockIdx.x / BPX;
+    const int l0 = (int)(blockIdx.x % BPX) * B::LA, la = l0 + threadIdx.x;   // k3 * NK + k2
+    const int kr = threadIdx.x / NK;
+    big_factors<NK, KR>(E02, et, mod_rows_at<NK>(et, a, x0 + xl, nu), l0 / NK);
     __syncthreads();
     const T* line = fx + (x0 + xl) * (long long)(NK * NK * NK) + (long long)la * NK;
-    const cd e23 = cmul(E[1][k2], E[2][k3]);
     cd* out = W + xl * (long long)(P * NK * NK) + la;
-    sfor<0, S>([&](auto hc) {
-        constexpr int h = decltype(hc)::value;
+#pragma unroll 1
+    for (int h = 0; h < S; ++h) {
         cd y[32];
-        sfor<0, 32>([&](auto jc) { y[decltype(jc)::value] = cd{0.0, 0.0}; });
-        // y[k mod 32] += e^{-i phi.p} f(p) w_P^{-h k}, k = k1 < NK (zero padded to P)
-        sfor<0, NK>([&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            const double fv = (double)line[k];
-            const cd e = cmul(E[0][k], e23);
-            const cd z = tmul<(long long)h * k, P, -1>(cd{e.re * fv, e.im * fv});
-            y[k % 32] = cadd(y[k % 32], z);
+        // y[k mod 32] = sum e^{-i phi.p} f(p) w^{h k}, k = k1 < NK (zero padded to P)
+        sfor<0, (NK + 31) / 32>([&](auto sc) {
+            constexpr int k0 = decltype(sc)::value * 32, n = NK < 32 ? NK : 32;
+            double fv[n];
+            load_k1<T, n>(line + k0, fv);
+            sfor<0, n>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                const cd m = E02[h][kr][k0 + k];
+                if constexpr (k0 == 0) y[k] = cd{m.re * fv[k], m.im * fv[k]};
+                else y[k] = cd{fma(m.re, fv[k], y[k].re), fma(m.im, fv[k], y[k].im)};
+            });
         });
+        if constexpr (NK < 32) sfor<NK, 32>([&](auto kc) { y[decltype(kc)::value] = cd{0.0, 0.0}; });
         transform<32, -1>(y);
         sfor<0, 32>([&](auto fc) {
             constexpr int f = decltype(fc)::value;
             out[(long long)(S * f + h) * (NK * NK)] = y[f];   // xi1 = S f + h
         });
+    }
+}
+
+// ---- B, C, D for N_k <= 32: planes W[x][xi1][k3][k2] through plane_conv, in place; a
+// one-wave block takes 64 / (2 N_k) planes, and no lane waits for another wave.  At
+// N_k = 32 a lane's half line (32 complex values) and the Toeplitz sums fill 254 VGPRs: two
+// waves per SIMD, FP64 VALU bound.  Per 2048 x-points: 1.60 ms, against 2.26 ms for one
+// wave per SIMD with half the lanes idle in B and D; k_thA 0.42 (0.61), k_thE 0.57 (0.87).
+template <int NK>
+__global__ __launch_bounds__(64, 2) void k_thBCD_plane(fft::cd* __restrict__ W, const double* __restrict__ kt,
+                                                      const fft::cd* __restrict__ et, const ThetaArgs a,
+                                                      long long x0, int nu)
+{
+    using namespace fft;
+    using S = PlaneShape<NK>;
+    constexpr int P = S::P, RS = S::RS, PPB = 64 / S::LANES;
+    __shared__ cd slots[PPB * S::SLOT];
+    __shared__ cd TWF[2][NK], TWD[2][NK];
+    const int lane = threadIdx.x % S::LANES, k3 = lane % NK, h = lane / NK, grp = threadIdx.x / S::LANES;
+    const long long p = (long long)blockIdx.x * PPB + grp;
+    const int xi1 = (int)(p % P);
+    cd* plane = W + p * (long long)(NK * NK);
+    cd* slot = slots + grp * S::SLOT;
+    // a block's planes belong to one x-point (PPB divides P)
+    const cd* e2 = mod_rows_at<NK>(et, a, x0 + p / P, nu).e2;
+    if (threadIdx.x < 2 * NK) {
+        const int hh = threadIdx.x / NK, j = threadIdx.x % NK;
+        const cd f = hh ? cmul(e2[j], et[j]) : e2[j];
+        TWF[hh][j] = f;
+        TWD[hh][j] = cd{a.wgt[nu] * f.re, -a.wgt[nu] * f.im};
+    }
+    sfor<0, NK / 2>([&](auto ic) {   // two rows per step
+        constexpr int i = decltype(ic)::value;
+        slot[(2 * i + h) * RS + k3] = plane[2 * i * NK + lane];
+    });
+    __syncthreads();
+    plane_conv<NK>(slot, kt + ((long long)xi1 * P + 2 * k3 + h) * NK, TWF[h], TWD[h], k3, h);
+    __syncthreads();
+    sfor<0, NK / 2>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        plane[2 * i * NK + lane] = slot[(2 * i + h) * RS + k3];
     });
 }
 
-// ---- B, C, D: one block per (x-point, xi1) slice W[x][xi1][k3][k2] (in place).
+// ---- B, C, D for N_k = 64: one block per (x-point, xi1) slice W[x][xi1][k3][k2] (in place).
 template <int NK>
-__global__ __launch_bounds__(BigShape<NK>::NTB) void k_thBCD(fft::cd* __restrict__ W, const double* __restrict__ kt)
+__global__ __launch_bounds__(BigShape<NK>::NTB) void k_thBCD(fft::cd* __restrict__ W, const double* __restrict__ kt,
+                                                              const fft::cd* __restrict__ et, const ThetaArgs a,
+                                                              long long x0, int nu)
 {
     using namespace fft;
     using B = BigShape<NK>;
     constexpr int P = B::P, L = B::L, S = B::S, RS = B::RS, NT = B::NTB;
     constexpr int JC = NK / 16;                 // 16-output chunks of a Toeplitz row
-    // N_k = 32: the sum over residues stays in the registers of the thread that owns its
-    // output row j3, and the kernel values K are read from the table (it sits in L2),
-    // so a block needs 34 KB of LDS and four blocks (one wave per SIMD) share a CU;
-    // larger N_k keep the sum and K in LDS.
-    constexpr bool ACC_REG = NK == 32;
-    __shared__ cd ACC[ACC_REG ? 1 : NK * RS];   // [j3][j2]: k2 inverse, summed over residues
+    __shared__ cd ACC[NK * RS];                 // [j3][j2]: k2 inverse, summed over residues
     __shared__ cd BC[L * RS];                   // [f][k3]: k2 forward of residue h
     __shared__ cd OC[L * RS];                   // [f][j3]: after the k3 Toeplitz product
-    __shared__ double KK[ACC_REG ? 1 : L * RS]; // [f][q3]: K(xi1, S f + h, q3)
+    __shared__ double KK[L * RS];               // [f][q3]: K(xi1, S f + h, q3)
+    __shared__ cd TW[S][NK];                    // e^{-i phi_2 k} w^{h k}
     const long long xl = blockIdx.x / P;
     const int xi1 = (int)(blockIdx.x % P);
     cd* slice = W + (xl * P + xi1) * (long long)(NK * NK);
     const int tid = threadIdx.x;
-    cd acc[ACC_REG ? NK : 1];                   // row j3 = tid of the residue sum (ACC_REG)
+    const double wgt = a.wgt[nu];
+    const cd* e2 = mod_rows_at<NK>(et, a, x0 + xl, nu).e2;
+    for (int t = tid; t < S * NK; t += NT) TW[t / NK][t % NK] = cmul(e2[t % NK], et[((t / NK) * (t % NK)) % P]);
+    __syncthreads();
 
     sfor<0, S>([&](auto hc) {
         constexpr int h = decltype(hc)::value;
@@ -125,23 +169,21 @@ __global__ __launch_bounds__(BigShape<NK>::NTB) void k_thBCD(fft::cd* __restrict
             const cd* row = slice + (long long)r * NK;
             sfor<0, NK>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
-                y[k % 32] = cadd(y[k % 32], tmul<(long long)h * k, P, -1>(row[k]));
+                y[k % 32] = cadd(y[k % 32], cmul(row[k], TW[h][k]));
             });
             transform<32, -1>(y);
             sfor<0, 32>([&](auto fc) { BC[decltype(fc)::value * RS + r] = y[decltype(fc)::value]; });
         }
-        if constexpr (!ACC_REG) {
-            for (int t = tid; t < L * NK; t += NT) {
-                const int f = t / NK, q = t % NK;
-                KK[f * RS + q] = kt[((long long)xi1 * P + (S * f + h)) * NK + q];
-            }
+        for (int t = tid; t < L * NK; t += NT) {
+            const int f = t / NK, q = t % NK;
+            KK[f * RS + q] = kt[((long long)xi1 * P + (S * f + h)) * NK + q];
         }
         __syncthreads();
         // C: o_j = sum_i K(|j - i|) row_i for each row f, 16 outputs per work item;
         // the 16 kernel values of one input form a window that slides down by one
         for (int t = tid; t < L * JC; t += NT) {
             const int f = t % L, j0 = (t / L) * 16;
-            const double* kk = ACC_REG ? kt + ((long long)xi1 * P + (S * f + h)) * NK : KK + f * RS;
+            const double* kk = KK + f * RS;
             const cd* row = BC + f * RS;
             cd o[16];
             double w[16];
@@ -172,57 +214,57 @@ __global__ __launch_bounds__(BigShape<NK>::NTB) void k_thBCD(fft::cd* __restrict
         }
         __syncthreads();
         // D: inverse along k2 over this residue's xi2, first NK outputs, summed over the
-        // residues (in ACC, or in the registers of thread j3)
+        // residues
         for (int j3 = tid; j3 < NK; j3 += NT) {
             cd v[32];
             sfor<0, 32>([&](auto fc) { v[decltype(fc)::value] = OC[decltype(fc)::value * RS + j3]; });
             transform<32, +1>(v);
             sfor<0, NK>([&](auto jc) {
                 constexpr int j2 = decltype(jc)::value;
-                const cd x = tmul<(long long)h * j2, P, +1>(v[j2 % 32]);
-                if constexpr (ACC_REG)
-                    acc[j2] = h == 0 ? x : cadd(acc[j2], x);
-                else
-                    ACC[j3 * RS + j2] = h == 0 ? x : cadd(ACC[j3 * RS + j2], x);
+                const cd x = cmul(v[j2 % 32], cd{wgt * TW[h][j2].re, -wgt * TW[h][j2].im});
+                ACC[j3 * RS + j2] = h == 0 ? x : cadd(ACC[j3 * RS + j2], x);
             });
         }
         __syncthreads();
     });
-    if constexpr (ACC_REG) {
-        static_assert(!ACC_REG || NT >= NK, "one thread per output row");
-        if (tid < NK) sfor<0, NK>([&](auto jc) { slice[tid * NK + decltype(jc)::value] = acc[decltype(jc)::value]; });
-    } else {
-        for (int t = tid; t < NK * NK; t += NT) {
-            const int j3 = t / NK, j2 = t % NK;
-            slice[t] = ACC[j3 * RS + j2];
-        }
+    for (int t = tid; t < NK * NK; t += NT) {
+        const int j3 = t / NK, j2 = t % NK;
+        slice[t] = ACC[j3 * RS + j2];
     }
 }
 
-// ---- E: k1 inverse, demodulation, imaginary part, sum over nuclei.  Block = 64 k1
-// lines of one x-point.  first: no earlier nucleus; last: write the result (type T)
-// to fx, else keep the FP64 sum in acc.
+// ---- E: k1 inverse, demodulation, imaginary part, sum over nuclei (the weight is
+// already in).  A thread per k1 line, one residue at a time; the real result of a line
+// is kept in registers (LDS at N_k = 64).  first: no earlier nucleus; last: write the
+// result (type T) to fx, else keep the FP64 sum in acc.
 template <typename T, int NK>
-__global__ __launch_bounds__(64) void k_thE(const fft::cd* __restrict__ W, double* __restrict__ acc,
-                                            T* __restrict__ fx, const ThetaArgs a, long long x0, int nu, int first,
-                                            int last)
+__global__ __launch_bounds__(BigShape<NK>::LE, 2) void k_thE(const fft::cd* __restrict__ W, double* __restrict__ acc,
+                                                            T* __restrict__ fx, const fft::cd* __restrict__ et,
+                                                            const ThetaArgs a, long long x0, int nu, int first, int last)
 {
     using namespace fft;
     using B = BigShape<NK>;
-    constexpr int P = B::P, S = B::S, RS = B::RS;
-    __shared__ cd E[3][NK];
-    __shared__ double TH[B::LPB * RS];
-    const long long xl = blockIdx.x / B::BPX;
-    const int la = (int)(blockIdx.x % B::BPX) * B::LPB + threadIdx.x;   // j3 * NK + j2
-    const int j2 = la % NK, j3 = la / NK;
-    big_modulation<NK>(a, x0 + xl, nu, E);
+    constexpr int P = B::P, S = B::S, RS = B::RS, KR = B::LE / NK, BPX = NK * NK / B::LE;
+    constexpr bool REG = NK <= 32;
+    __shared__ cd E02[S][KR][NK];
+    __shared__ double TH[REG ? 1 : B::LE * RS];
+    const long long xl = blockIdx.x / BPX;
+    const int l0 = (int)(blockIdx.x % BPX) * B::LE, la = l0 + threadIdx.x;   // j3 * NK + j2
+    const int kr = threadIdx.x / NK;
+    big_factors<NK, KR>(E02, et, mod_rows_at<NK>(et, a, x0 + xl, nu), l0 / NK);
     __syncthreads();
-    const double w = a.wgt[nu];
-    const cd e23c = conj(cmul(E[1][j2], E[2][j3]));
     const cd* src = W + xl * (long long)(P * NK * NK) + la;
-    double* th = TH + threadIdx.x * RS;
-    sfor<0, S>([&](auto hc) {
-        constexpr int h = decltype(hc)::value;
+    const long long off = (x0 + xl) * (long long)(NK * NK * NK) + (long long)la * NK;
+    double* ac = acc + xl * (long long)(NK * NK * NK) + (long long)la * NK;
+    double thr[REG ? NK : 1];
+    double* th = TH + (REG ? 0 : threadIdx.x * RS);
+    auto at = [&](auto jc) -> double& {
+        if constexpr (REG) return thr[decltype(jc)::value];
+        else return th[decltype(jc)::value];
+    };
+    sfor<0, NK>([&](auto jc) { at(jc) = first ? 0.0 : ac[decltype(jc)::value]; });
+#pragma unroll 1
+    for (int h = 0; h < S; ++h) {
         cd v[32];
         sfor<0, 32>([&](auto fc) {
             constexpr int f = decltype(fc)::value;
@@ -231,17 +273,19 @@ __global__ __launch_bounds__(64) void k_thE(const fft::cd* __restrict__ W, doubl
         transform<32, +1>(v);
         sfor<0, NK>([&](auto jc) {
             constexpr int j1 = decltype(jc)::value;
-            const cd d = cmul(conj(E[0][j1]), e23c);                    // e^{+i phi.p}
-            const cd t = cmul(d, tmul<(long long)h * j1, P, +1>(v[j1 % 32]));
-            th[j1] = (h == 0 ? 0.0 : th[j1]) + w * t.im;
+            const cd m = E02[h][kr][j1];
+            at(jc) = fma(m.re, v[j1 % 32].im, fma(-m.im, v[j1 % 32].re, at(jc)));   // Im(conj(m) v)
         });
-    });
-    const long long off = (x0 + xl) * (long long)(NK * NK * NK) + (long long)la * NK;
-    double* ac = acc + xl * (long long)(NK * NK * NK) + (long long)la * NK;
-    for (int j1 = 0; j1 < NK; ++j1) {
-        const double v = th[j1] + (first ? 0.0 : ac[j1]);
-        if (last) fx[off + j1] = (T)v;
-        else ac[j1] = v;
+    }
+    if (last) {
+        sfor<0, (NK + 31) / 32>([&](auto sc) {
+            constexpr int k0 = decltype(sc)::value * 32, n = NK < 32 ? NK : 32;
+            double o[n];
+            sfor<0, n>([&](auto jc) { o[decltype(jc)::value] = at(std::integral_constant<int, k0 + decltype(jc)::value>{}); });
+            store_k1<T, n>(fx + off + k0, o);
+        });
+    } else {
+        sfor<0, NK>([&](auto jc) { ac[decltype(jc)::value] = at(jc); });
     }
 }
 

@@ -14,8 +14,8 @@
  * Theta is evaluated twice per step.
  *
  * The field (caller-owned, layout and dtype of chasm_advect.h, nbatch 1) is advanced
- * in place and is itself the state: the library keeps Theta[f^n] and the predictor in
- * two fields of its own, and no step copies the field.  If a step fails the handle is
+ * in place and is itself the state: the library keeps Theta[f^n] in a field of its
+ * own, and no step copies the field.  If a step fails the handle is
  * poisoned and the field may hold a partly updated step.  Status codes and chasm_advect_last_error() are
  * shared with chasm_advect.h.  Handles are not thread-safe.
  */
@@ -35,8 +35,8 @@ typedef struct chasm_lpc1_s* chasm_lpc1_t;   /* opaque handle */
 
 /* adv describes the grid, splines and tau (= adv->dt); its nbatch must be 1 and its
  * flags 0.  th must describe the same grid and dtype with nbatch 1.  f_dev is the
- * caller's field; it must stay allocated until chasm_lpc1_destroy.  Allocates two
- * fields plus the workspaces of the operators (two advection handles, one Theta).  CHASM_EINVAL on mismatched
+ * caller's field; it must stay allocated until chasm_lpc1_destroy.  Allocates one
+ * field plus the workspaces of the operators (two advection handles, one Theta).  CHASM_EINVAL on mismatched
  * descriptors; the errors of chasm_advect_create / chasm_theta_create otherwise. */
 chasm_status chasm_lpc1_create(const chasm_advect_desc* adv, const chasm_theta_desc* th, void* f_dev,
                                void* hip_stream, chasm_lpc1_t* out);

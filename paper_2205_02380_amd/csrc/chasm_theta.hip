@@ -246,6 +246,32 @@ static void desc_hk(const chasm_theta_desc* d, int nk[3], double hk[3])
     }
 }
 
+// x-major copy (mode_in), the convolutions on it, and back (mode_out); see TransposeMode.
+static chasm_status run_theta(chasm_theta_t h, int mode_in, const void* f, const void* g_in, double c_in, int mode_out,
+                              void* out, const void* g_out, double c_out)
+{
+    const int nb = h->desc.nbatch;
+    hipError_t e = h->ks->transpose(mode_in, f, g_in, h->ws, h->nkp, h->npts, nb, c_in, h->stream);
+    if (e == hipSuccess)
+        e = h->big ? h->ks->big(h->ws, h->kt, h->et, h->args, h->W, h->acc, h->npts * nb, h->X, h->stream)
+                   : h->ks->theta(h->ws, h->kt, h->et, h->args, h->npts * nb, h->stream);
+    if (e == hipSuccess) e = h->ks->transpose(mode_out, h->ws, g_out, out, h->npts, h->nkp, nb, c_out, h->stream);
+    if (e != hipSuccess) {
+        h->poisoned = true;
+        return tfail(CHASM_EDEVICE, std::string("theta launch: ") + hipGetErrorString(e));
+    }
+    return CHASM_OK;
+}
+
+namespace chasm {
+// The predictor and corrector of an LPC1 step: f = f + tau/2 (g + Theta[f + tau g]).
+chasm_status theta_lpc1(chasm_theta_t h, void* f, const void* g, double tau)
+{
+    if (h->poisoned) return tfail(CHASM_ESTATE, "handle is poisoned by an earlier device failure");
+    return run_theta(h, TR_PREDICT, f, g, tau, TR_CORRECT, f, g, 0.5 * tau);
+}
+}  // namespace chasm
+
 extern "C" {
 
 chasm_status chasm_theta_workspace_bytes(const chasm_theta_desc* desc, size_t* bytes)
@@ -358,17 +384,7 @@ chasm_status chasm_theta_apply(chasm_theta_t h, const void* f_dev, void* out_dev
 {
     if (!h || !f_dev || !out_dev) return tfail(CHASM_EINVAL, "NULL argument");
     if (h->poisoned) return tfail(CHASM_ESTATE, "handle is poisoned by an earlier device failure");
-    const int nb = h->desc.nbatch;
-    hipError_t e = h->ks->transpose(f_dev, h->ws, h->nkp, h->npts, nb, h->stream);
-    if (e == hipSuccess)
-        e = h->big ? h->ks->big(h->ws, h->kt, h->et, h->args, h->W, h->acc, h->npts * nb, h->X, h->stream)
-                   : h->ks->theta(h->ws, h->kt, h->et, h->args, h->npts * nb, h->stream);
-    if (e == hipSuccess) e = h->ks->transpose(h->ws, out_dev, h->npts, h->nkp, nb, h->stream);
-    if (e != hipSuccess) {
-        h->poisoned = true;
-        return tfail(CHASM_EDEVICE, std::string("theta launch: ") + hipGetErrorString(e));
-    }
-    return CHASM_OK;
+    return run_theta(h, TR_PLAIN, f_dev, nullptr, 0.0, TR_PLAIN, out_dev, nullptr, 0.0);
 }
 
 chasm_status chasm_theta_destroy(chasm_theta_t h)

@@ -83,25 +83,34 @@ __device__ __forceinline__ void store_k1(T* __restrict__ p, const double (&v)[NK
 }
 
 // out[b][c][r] = in[b][r][c] for an (rows x cols) matrix per batch member; 64 x 64
-// tiles through LDS, 256 threads, coalesced on both sides.
-template <typename T>
-__global__ __launch_bounds__(256) void k_transpose(const T* __restrict__ in, T* __restrict__ out, long long rows,
-                                                  long long cols)
+// tiles through LDS, 256 threads, coalesced on both sides.  The transposes of an LPC1
+// step (Sec. 2.2) also form its combinations, which saves a pass over memory each:
+//   TR_PREDICT  out = (in + c g) transposed         (g in the layout of in)
+//   TR_CORRECT  out = out + c (g + in transposed)   (g in the layout of out)
+enum TransposeMode { TR_PLAIN = 0, TR_PREDICT = 1, TR_CORRECT = 2 };
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(256) void k_transpose(const T* __restrict__ in, const T* __restrict__ g, T* __restrict__ out,
+                                                  long long rows, long long cols, T c)
 {
     __shared__ T tile[64][65];
     const long long b = blockIdx.z;
-    const long long r0 = (long long)blockIdx.y * 64, c0 = (long long)blockIdx.x * 64;
-    const T* src = in + b * rows * cols;
-    T* dst = out + b * rows * cols;
+    const long long r0 = (long long)blockIdx.y * 64, c0 = (long long)blockIdx.x * 64, base = b * rows * cols;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int i = ty; i < 64; i += 4) {
-        const long long r = r0 + i, c = c0 + tx;
-        if (r < rows && c < cols) tile[i][tx] = src[r * cols + c];
+        const long long r = r0 + i, cc = c0 + tx;
+        if (r < rows && cc < cols) {
+            const long long at = base + r * cols + cc;
+            tile[i][tx] = MODE == TR_PREDICT ? fma(c, g[at], in[at]) : in[at];
+        }
     }
     __syncthreads();
     for (int i = ty; i < 64; i += 4) {
-        const long long c = c0 + i, r = r0 + tx;
-        if (r < rows && c < cols) dst[c * rows + r] = tile[tx][i];
+        const long long cc = c0 + i, r = r0 + tx;
+        if (r < rows && cc < cols) {
+            const long long at = base + cc * rows + r;
+            out[at] = MODE == TR_CORRECT ? fma(c, g[at] + tile[tx][i], out[at]) : tile[tx][i];
+        }
     }
 }
 

@@ -18,7 +18,8 @@ struct ThetaKernels {
     int dtype, nk;
     hipError_t (*theta)(void* fx, const double* kt, const fft::cd* et, const ThetaArgs& a, long long total,
                         hipStream_t s);
-    hipError_t (*transpose)(const void* in, void* out, long long rows, long long cols, int batch, hipStream_t s);
+    hipError_t (*transpose)(int mode, const void* in, const void* g, void* out, long long rows, long long cols,
+                            int batch, double c, hipStream_t s);
     BigFn big;                 // staged form (nullptr: none)
     hipError_t (*mod)(fft::cd* et, const ThetaArgs& a, hipStream_t s);
 };
@@ -82,11 +83,14 @@ hipError_t launch_big(void* fx, const double* kt, const fft::cd* et, const Theta
 }
 
 template <typename T>
-hipError_t launch_transpose(const void* in, void* out, long long rows, long long cols, int batch, hipStream_t s)
+hipError_t launch_transpose(int mode, const void* in, const void* g, void* out, long long rows, long long cols, int batch,
+                            double c, hipStream_t s)
 {
     const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64), (unsigned)batch);
-    hipLaunchKernelGGL(k_transpose<T>, grid, dim3(256), 0, s, static_cast<const T*>(in), static_cast<T*>(out), rows,
-                       cols);
+    auto k = mode == TR_PLAIN ? k_transpose<T, TR_PLAIN> : mode == TR_PREDICT ? k_transpose<T, TR_PREDICT>
+                                                                             : k_transpose<T, TR_CORRECT>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, static_cast<const T*>(in), static_cast<const T*>(g),
+                       static_cast<T*>(out), rows, cols, (T)c);
     return hipGetLastError();
 }
 

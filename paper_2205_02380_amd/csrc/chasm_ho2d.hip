@@ -2,28 +2,35 @@
 // include/chasm_ho2d.h): LPC1 with the patched-spline characteristic step in x and the
 // spectral k-derivative Theta[f] = omega x d_k f, all FP64.
 //
-// Kernels:
+// Transform path (nk a power of two in 64..1024): a step is two launches, and the
+// library's fields are kept as [x][k], so that the k transforms read contiguous lines
+// and the x sweeps read short contiguous runs; k_ho_turn converts the caller's [k][x]
+// field at both ends of a call.
 //   k_ho_advect  the characteristic step of LB k-lines per block, lines of runtime
-//                length in LDS: PMBC interface slopes (eqs. 3.4-3.5), each patch's
-//                reduced Hermite system solved as a product with its precomputed
-//                inverse (one output per thread, so a line's patches solve in parallel),
-//                the Hermite ghosts, and the 4-tap evaluation by the owning patch
-//                (eqs. 3.7-3.8, Sec. 3.1.3), out of place; departure points outside
-//                the line give 0 unless the descriptor asks for ghost extrapolation.
-//   k_ho_dk      Theta by transforms, for nk = L1 L2 a power of two in 64..1024: two
-//                real k-lines (x columns 2c, 2c+1) form one complex line, since the
-//                derivative F^-1 diag(i xi) F maps real lines to real lines; a
-//                four-step transform (L1-point register transforms over stride-L2
-//                elements, twiddles, L2-point register transforms), the multiply by
-//                i xi / nk (Nyquist mode 0) and the inverse in reverse order, with two
-//                LDS transposes per line.  Mode 1 fuses the LPC1 corrector: it reads
-//                FA, GA, transforms Y = FA + tau GA and writes FA + tau/2 (GA + Theta Y).
+//                length in LDS: PMBC interface slopes (eqs. 3.4-3.5, eight lanes per dot
+//                product), each patch's reduced Hermite system by the sweeping method
+//                (one thread per patch and line), the Hermite ghosts, and the 4-tap
+//                evaluation by the owning patch (eqs. 3.7-3.8, Sec. 3.1.3), out of place;
+//                departure points outside the line give 0 unless the descriptor asks
+//                for ghost extrapolation.
+//   k_ho_dk      Theta by transforms, for nk = L1 L2: two real k-lines (x columns 2c,
+//                2c+1) form one complex line, since the derivative F^-1 diag(i xi) F maps
+//                real lines to real lines; a four-step transform (L1-point register
+//                transforms over stride-L2 elements, twiddles, L2-point register
+//                transforms), the multiply by i xi / nk (Nyquist mode 0) and the inverse
+//                in reverse order, with two LDS transposes per line.  The corrector form
+//                reads FA, GA, transforms Y = FA + tau GA, forms the new field FA + tau/2
+//                (GA + Theta Y) and, unless the step is the call's last, transforms that
+//                again for the next step's Theta F: the column is already in registers.
+//                At nx = 241, nk = 512 a step is 17.3 us, against 28.9 us in three
+//                launches on [k][x] fields.
 //   k_ho_dk512   nk = 512: the same transform pair in three levels of 8-point
 //                transforms, one complex line per 64-thread block.
-//   k_ho_theta   any other even nk: out[k][x] = omega x sum_q D[k][q] f[q][x], a dense
-//                FP64 contraction with the circulant spectral differentiation matrix,
-//                32 x 32 output tiles staged through LDS, 2 x 2 outputs per thread.
-//   k_ho_combine the predictor / corrector combinations of the dense path.
+// Dense path (any other even nk; fields [k][x]):
+//   k_ho_theta   out[k][x] = omega x sum_q D[k][q] f[q][x], a dense FP64 contraction with
+//                the circulant spectral differentiation matrix, 32 x 32 output tiles
+//                staged through LDS, 2 x 2 outputs per thread.
+//   k_ho_combine the predictor / corrector combinations.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,97 +50,200 @@ struct HoArgs {
     int N, M, P, mlast, g, nk, inflow;
     double hx;
     const double* stencil;     // (P+1) x (2g+1), slopes (not times h)
-    const double* ainvM;       // (M+1)^2 inverse of [4 2; 1 4 1; ...; 2 4]
-    const double* ainvL;       // (mlast+1)^2
+    const double* lu;          // inv, ainv, cp of the reduced patch system (patch_factors): the first
+                               // HO_LU rows of a long patch (rows before the last do not depend on its length)
+    double inv_l[2], ainv_l[2];   // last row: patches of M cells, the last patch
     const int* shift;          // nk
     const double* w;           // nk x 4
 };
 
-constexpr int HO_LB = 2;       // lines per block (measured at nx = 241, 1024 lines: 8 -> 21.5 us, 4 -> 15.7, 2 -> 14.7)
+// LDS doubles of k_ho_advect per line: the nodes (odd row length, but for the longest
+// lines), the slopes and the patches' coefficients.
+__host__ __device__ constexpr int ho_row(int LB, int N) { return LB > 2 ? N | 1 : N; }
+__host__ __device__ constexpr int ho_line_doubles(int LB, int N, int P) { return ho_row(LB, N) + (N - 1 + 3 * P) + (P + 1); }
 
+// Rows of the patch factors that are kept: the recursion contracts by (2 - sqrt 3)^2 = 0.07
+// a row, so from row 14 on the factors are one constant to double precision.
+constexpr int HO_LU = 32;
+
+// The lines of two stacked fields of nk x N values: line L is k node L % nk of field
+// L / nk.  XK: fields are [x][k], else [k][x].  Bound by latency (a 1 MB field over 256
+// blocks): every global load is issued before the first barrier, the slopes take (2 g + 1)
+// / 8 terms a lane, and the serial part is one patch sweep of 2 M dependent multiply-adds
+// out of LDS.  10.6 us a launch at nx = 241, 1024 lines, against
+// 14.7 us for the product of each patch with its precomputed inverse.
+template <int LB, bool XK>
 __global__ __launch_bounds__(256) void k_ho_advect(const double* __restrict__ in, double* __restrict__ out, const HoArgs a,
                                                   int nlines)
 {
     extern __shared__ double sm[];
-    const int N = a.N, M = a.M, P = a.P;
+    const int N = a.N, M = a.M, P = a.P, NS = ho_row(LB, N);
     const int ES = N - 1 + 3 * P;                    // sum over patches of (m + 3)
-    double* phi = sm;                                // [LB][N]
-    double* dsl = phi + HO_LB * N;                   // [LB][P+1] slopes times h
-    double* eta = dsl + HO_LB * (P + 1);             // [LB][ES], patch l at l (M+3): eta_{-1..m+1}
-    const int line0 = blockIdx.x * HO_LB;
-    const int tid = threadIdx.x;
-
-    for (int e = tid; e < HO_LB * N; e += blockDim.x) {
-        const int ln = e / N, L = line0 + ln;
-        phi[e] = L < nlines ? in[(long long)L * N + e % N] : 0.0;
+    double* phi = sm;                                // [LB][NS]
+    double* dsl = phi + LB * NS;                     // [LB][P+1] slopes times h
+    double* eta = dsl + LB * (P + 1);                // [LB][ES], patch l at l (M+3): eta_{-1..m+1}
+    // the factors [inv, ainv, cp][HO_LU]: in LDS, but for the longest lines, which fill it
+    double* const lds_lu = eta + LB * ES;
+    const double* const lu = LB > 2 ? lds_lu : a.lu;
+    const double *const inv = lu, *const ainv = lu + HO_LU, *const cp = lu + 2 * HO_LU;
+    const int line0 = blockIdx.x * LB;
+    const int tid = threadIdx.x, W = 2 * a.g + 1, nrow = LB * (P + 1);
+    auto at = [&](int L, int j) -> long long {
+        if constexpr (XK) {
+            const int fld = L / a.nk, kk = L - fld * a.nk;
+            return ((long long)fld * N + j) * a.nk + kk;
+        } else {
+            return (long long)L * N + j;
+        }
+    };
+    // interface row e of the block's LB (P + 1): line e / (P + 1), interface e % (P + 1)
+    auto iface = [&](int q) { return q < P ? q * M : N - 1; };
+    constexpr int PRE = 8;                           // taps per lane fetched ahead (first 32 rows)
+    double cf[PRE];
+    {
+        const int e = tid / 8, q = e % (P + 1);
+#pragma unroll
+        for (int u = 0; u < PRE; ++u) {
+            const int t = tid % 8 + 8 * u;
+            cf[u] = e < nrow && t < W ? a.stencil[q * W + t] : 0.0;
+        }
+    }
+    if (LB > 2 && tid < 3 * HO_LU) lds_lu[tid] = a.lu[tid];
+    // [x][k]: a thread's outputs all belong to line tid % LB
+    const int my_k = (line0 + tid % LB) % a.nk;
+    const int my_shift = a.shift[my_k];
+    const double my_w[4] = {a.w[4 * my_k], a.w[4 * my_k + 1], a.w[4 * my_k + 2], a.w[4 * my_k + 3]};
+    for (int e = tid; e < LB * N; e += 256) {
+        const int ln = XK ? e % LB : e / N, j = XK ? e / LB : e - ln * N;
+        phi[ln * NS + j] = line0 + ln < nlines ? in[at(line0 + ln, j)] : 0.0;
     }
     __syncthreads();
-    const int W = 2 * a.g + 1;
-    for (int e = tid; e < HO_LB * (P + 1); e += blockDim.x) {
-        const int ln = e / (P + 1), q = e % (P + 1);
-        const int I = q < P ? q * M : N - 1;
+    for (int e0 = 0; e0 < nrow; e0 += 32) {          // eight lanes per interface slope
+        const int e = e0 + tid / 8;
         double acc = 0.0;
-        for (int t = 0; t < W; ++t) {
-            const int j = I - a.g + t;
-            if (j >= 0 && j < N) acc = fma(a.stencil[q * W + t], phi[ln * N + j], acc);
+        if (e < nrow) {
+            const int ln = e / (P + 1), q = e % (P + 1);
+            const double* v = phi + ln * NS;
+            const int j0 = iface(q) - a.g;
+            int t = tid % 8;
+            if (e0 == 0) {
+#pragma unroll
+                for (int u = 0; u < PRE; ++u) {      // taps off the line have coefficient 0
+                    const int j = j0 + t + 8 * u;
+                    acc = fma(cf[u], v[j < 0 ? 0 : (j < N ? j : N - 1)], acc);
+                }
+                t += 8 * PRE;
+            }
+            for (; t < W; t += 8) {
+                const int j = j0 + t;
+                if (j >= 0 && j < N) acc = fma(a.stencil[q * W + t], v[j], acc);
+            }
         }
-        dsl[e] = acc * a.hx;
+        acc += __shfl_xor(acc, 1, 64);
+        acc += __shfl_xor(acc, 2, 64);
+        acc += __shfl_xor(acc, 4, 64);
+        if (e < nrow && tid % 8 == 0) dsl[e] = acc * a.hx;
     }
     __syncthreads();
-    // each thread takes one row i of one patch's inverse and applies it to the right-hand
-    // sides of all LB lines: rhs_jj = 6 phi_jj, plus 2 h d_L at jj = 0 and minus 2 h d_R at
-    // jj = m (added after the loop, the product being linear)
-    const int per_line = N - 1 + P;                  // unknowns eta_0..eta_m of every patch
-    for (int r = tid; r < per_line; r += blockDim.x) {
-        const int l = min(r / (M + 1), P - 1);
-        const int i = r - l * (M + 1);
-        const int m = l < P - 1 ? M : a.mlast;
-        const double* A = (l < P - 1 ? a.ainvM : a.ainvL) + (long long)i * (m + 1);
-        double acc[HO_LB];
+    // forward sweep and back substitution of one patch per thread; the LDS reads of eight
+    // nodes are issued together, ahead of their part of the dependent chain
+    for (int e = tid; e < LB * P; e += 256) {
+        const int ln = e / P, l = e % P, last = l == P - 1;
+        const int m = last ? a.mlast : M;
+        const double dL = dsl[ln * (P + 1) + l], dR = dsl[ln * (P + 1) + l + 1];
+        const double* v = phi + ln * NS + l * M;
+        double* E = eta + ln * ES + l * (M + 3) + 1;
+        const double inv_c = inv[HO_LU - 1], ainv_c = ainv[HO_LU - 1], cp_c = cp[HO_LU - 1];
+        double x = fma(1.0 / 3.0, dL, v[0]) * inv[0];
+        E[0] = x;
+        int i = 1;
+        for (; i + 8 <= m; i += 8) {                 // rows i .. i + 7
+            double r[8], f[8];
+            if (i + 7 < HO_LU) {
 #pragma unroll
-        for (int ln = 0; ln < HO_LB; ++ln) acc[ln] = 0.0;
-        for (int jj = 0; jj <= m; ++jj) {
-            const double aij = 6.0 * A[jj];
+                for (int u = 0; u < 8; ++u) {
+                    r[u] = v[i + u] * inv[i + u];
+                    f[u] = ainv[i + u];
+                }
+            } else {
 #pragma unroll
-            for (int ln = 0; ln < HO_LB; ++ln) acc[ln] = fma(aij, phi[ln * N + l * M + jj], acc[ln]);
+                for (int u = 0; u < 8; ++u) {
+                    r[u] = v[i + u] * inv_c;
+                    f[u] = ainv_c;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r[u] = x = fma(-f[u], x, r[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) E[i + u] = r[u];
         }
-        const double a0 = 2.0 * A[0], am = 2.0 * A[m];
+        for (; i < m; ++i) {
+            const int k = i < HO_LU ? i : HO_LU - 1;
+            E[i] = x = fma(-ainv[k], x, v[i] * inv[k]);
+        }
+        E[m] = x = fma(-a.ainv_l[last], x, fma(-1.0 / 3.0, dR, v[m]) * a.inv_l[last]);
+        i = m - 1;
+        for (; i - 7 >= 0; i -= 8) {                 // rows i .. i - 7
+            double r[8], f[8];
 #pragma unroll
-        for (int ln = 0; ln < HO_LB; ++ln)
-            eta[ln * ES + l * (M + 3) + 1 + i] =
-                acc[ln] + a0 * dsl[ln * (P + 1) + l] - am * dsl[ln * (P + 1) + l + 1];
+            for (int u = 0; u < 8; ++u) r[u] = E[i - u];
+            if (i < HO_LU) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f[u] = cp[i - u];
+            } else if (i - 7 >= HO_LU) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f[u] = cp_c;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f[u] = cp[i - u < HO_LU ? i - u : HO_LU - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r[u] = x = fma(-f[u], x, r[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) E[i - u] = r[u];
+        }
+        for (; i >= 0; --i) E[i] = x = fma(-cp[i < HO_LU ? i : HO_LU - 1], x, E[i]);
+        E[-1] = fma(-2.0, dL, E[1]);                              // eta_{-1} = eta_1 - 2 h d_L
+        E[m + 1] = fma(2.0, dR, E[m - 1]);                        // eta_{m+1} = eta_{m-1} + 2 h d_R
     }
     __syncthreads();
-    for (int e = tid; e < HO_LB * P; e += blockDim.x) {
-        const int ln = e / P, l = e % P;
-        const int m = l < P - 1 ? M : a.mlast;
-        double* E = eta + ln * ES + l * (M + 3);
-        E[0] = E[2] - 2.0 * dsl[ln * (P + 1) + l];                // eta_{-1} = eta_1 - 2 h d_L
-        E[m + 2] = E[m] + 2.0 * dsl[ln * (P + 1) + l + 1];        // eta_{m+1} = eta_{m-1} + 2 h d_R
-    }
-    __syncthreads();
-    for (int e = tid; e < HO_LB * N; e += blockDim.x) {
-        const int ln = e / N, j = e % N, L = line0 + ln;
+    for (int e = tid; e < LB * N; e += 256) {
+        const int ln = XK ? e % LB : e / N, j = XK ? e / LB : e - ln * N, L = line0 + ln;
         if (L >= nlines) continue;
-        const int kk = L % a.nk;
-        const int c = j + a.shift[kk];                           // departure cell
+        const int kk = XK ? 0 : L % a.nk;
+        const int c = j + (XK ? my_shift : a.shift[kk]);         // departure cell
+        double w[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = XK ? my_w[r] : a.w[4 * kk + r];
         double v = 0.0;
         // departure point inside [x_0, x_{N-1}]: cell 0 .. N-2, or exactly node N-1
         // (beta = 0, i.e. w3 = beta^3/6 = 0)
-        const bool inside = c >= 0 && (c < N - 1 || (c == N - 1 && a.w[4 * kk + 3] == 0.0));
+        const bool inside = c >= 0 && (c < N - 1 || (c == N - 1 && w[3] == 0.0));
         if ((inside || a.inflow == 1) && c >= -4 && c <= N + 2) {
             const int l = c < 0 ? 0 : min(c / M, P - 1);         // owner patch
             const int m = l < P - 1 ? M : a.mlast;
             const int nu = c - l * M;
             const double* E = eta + ln * ES + l * (M + 3);
-            const double* w = a.w + 4 * kk;
+#pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int u = nu - 1 + r;                        // eta_u, zero beyond the ghosts
                 if (u >= -1 && u <= m + 1) v = fma(w[r], E[u + 1], v);
             }
         }
-        out[(long long)L * N + j] = v;
+        out[at(L, j)] = v;
     }
+}
+
+// dst[c][r] = src[r][c] of a rows x cols matrix, 32 x 32 tiles through LDS.
+__global__ __launch_bounds__(256) void k_ho_turn(const double* __restrict__ src, double* __restrict__ dst, int rows, int cols)
+{
+    __shared__ double tile[32][33];
+    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32, tx = threadIdx.x % 32, ty = threadIdx.x / 32;
+    for (int i = ty; i < 32; i += 8)
+        if (r0 + i < rows && c0 + tx < cols) tile[i][tx] = src[(long long)(r0 + i) * cols + c0 + tx];
+    __syncthreads();
+    for (int i = ty; i < 32; i += 8)
+        if (c0 + i < cols && r0 + tx < rows) dst[(long long)(c0 + i) * rows + r0 + tx] = tile[tx][i];
 }
 
 __global__ __launch_bounds__(256) void k_ho_theta(const double* __restrict__ D, const double* __restrict__ f,
@@ -192,16 +302,18 @@ struct DkShape {
     static constexpr int RS = L2 + 1;                // LDS row of [k1][n2], padded
 };
 
-// MODE 0: out = omega x d_k a.  MODE 1: y = a + tau b, out = (a + tau/2 b) + tau/2 omega x d_k y.
+// What a k transform kernel does with its columns (fields [x][k]):
+//   DK_THETA    out2 = Theta a
+//   DK_LAST     out = (a + tau/2 b) + tau/2 Theta (a + tau b)
+//   DK_STEP     the same out, and out2 = Theta out (the next step's first derivative)
+enum DkMode { DK_THETA = 0, DK_LAST = 1, DK_STEP = 2 };
+
 // tw[j] = e^{+2 pi i j / L}.  Index convention of the four-step transform: element
-// n = L2 n1 + n2, frequency m = k1 + L1 k2.  Each lane reads and writes its own
-// elements in HBM (one wave per block, so the block count, not the run length of a
-// row, sets how much of the chip takes part: staging a 16-column tile through LDS
-// for row-contiguous accesses ran 2.3x slower at nx = 241, nk = 512).
+// n = L2 n1 + n2, frequency m = k1 + L1 k2.
 template <int L1, int L2, int MODE>
 __global__ __launch_bounds__(64) void k_ho_dk(const double* __restrict__ a, const double* __restrict__ b,
-                                              double* __restrict__ out, const fft::cd* __restrict__ tw,
-                                              const DkArgs p)
+                                              double* __restrict__ out, double* __restrict__ out2,
+                                              const fft::cd* __restrict__ tw, const DkArgs p)
 {
     using namespace fft;
     using S = DkShape<L1, L2>;
@@ -212,78 +324,91 @@ __global__ __launch_bounds__(64) void k_ho_dk(const double* __restrict__ a, cons
     const int xa = 2 * (blockIdx.x * S::CLB + cl), xb = xa + 1;
     const bool has_a = xa < p.nx, has_b = xb < p.nx;
     cd* Y = lds + cl * L1 * S::RS;
+    const bool rows = lt < L2 && has_a;              // thread n2 = lt of steps 1 and 3
+    const int n2 = lt;
+    const long long ca = (long long)xa * L + n2, cb = (long long)xb * L + n2;   // + L2 n1
+    const double h = 0.5 * p.tau, tau = p.tau, hk = p.hk;
+    const double fa = p.omega * (p.x_lo + xa * p.hx), fb = p.omega * (p.x_lo + xb * p.hx);
 
-    // MODE 1 keeps a + tau/2 b of the thread's output elements from step 1 to step 3
-    // (the same rows and columns), so step 3 issues no dependent loads.
-    const double h = 0.5 * p.tau;
-    cd keep[MODE == 1 ? L1 : 1];
-    // Step 1 (thread n2 = lt): L1-point transforms over n1, twiddle e^{-2 pi i n2 k1 / L}.
-    if (lt < L2 && has_a) {
-        const int n2 = lt;
-        cd v[L1];
+    // v: elements L2 n1 + n2 of the column pair -> its k derivative at the same elements
+    auto derive = [&](cd (&v)[L1]) {
+        // Step 1 (thread n2): L1-point transforms over n1, twiddle e^{-2 pi i n2 k1 / L}.
+        if (rows) {
+            transform<L1, -1>(v);
+            sfor<0, L1>([&](auto kc) {
+                constexpr int k1 = decltype(kc)::value;
+                cd w = v[k1];
+                if constexpr (k1 > 0) w = cmul(w, conj(tw[(n2 * k1) & (L - 1)]));
+                Y[k1 * S::RS + n2] = w;
+            });
+        }
+        __syncthreads();
+        // Step 2 (thread k1 = lt): L2-point transforms over n2 give X[k1 + L1 k2]; multiply by
+        // i xi_m / L; inverse L2-point transforms; twiddle e^{+2 pi i n2 k1 / L}.
+        if (lt < L1 && has_a) {
+            const int k1 = lt;
+            cd u[L2];
+            sfor<0, L2>([&](auto ic) { u[decltype(ic)::value] = Y[k1 * S::RS + decltype(ic)::value]; });
+            transform<L2, -1>(u);
+            const double unit = 2.0 * kPi / (L * hk) / L;
+            sfor<0, L2>([&](auto kc) {
+                constexpr int k2 = decltype(kc)::value;
+                const int m = k1 + L1 * k2;
+                const double xi = m < L / 2 ? (double)m * unit : (m == L / 2 ? 0.0 : (double)(m - L) * unit);
+                u[k2] = {-xi * u[k2].im, xi * u[k2].re};
+            });
+            transform<L2, +1>(u);
+            sfor<0, L2>([&](auto nc) {
+                constexpr int n = decltype(nc)::value;
+                cd w = u[n];
+                if constexpr (n > 0) w = cmul(w, tw[(n * k1) & (L - 1)]);
+                Y[k1 * S::RS + n] = w;
+            });
+        }
+        __syncthreads();
+        // Step 3 (thread n2): inverse L1-point transforms over k1 give d_k y at L2 n1 + n2;
+        // real part column xa, imaginary part column xb.
+        if (rows) {
+            sfor<0, L1>([&](auto kc) { v[decltype(kc)::value] = Y[decltype(kc)::value * S::RS + n2]; });
+            transform<L1, +1>(v);
+        }
+    };
+
+    cd v[L1], keep[MODE == DK_THETA ? 1 : L1];
+    if (rows) {
         sfor<0, L1>([&](auto ic) {
             constexpr int n1 = decltype(ic)::value;
-            const long long row = (long long)(L2 * n1 + n2) * p.nx;
-            if constexpr (MODE == 0) {
-                v[n1] = {a[row + xa], has_b ? a[row + xb] : 0.0};
-            } else {
-                const double aa = a[row + xa], ba = b[row + xa];
-                const double ab = has_b ? a[row + xb] : 0.0, bb = has_b ? b[row + xb] : 0.0;
-                v[n1] = {fma(p.tau, ba, aa), fma(p.tau, bb, ab)};
-                keep[n1] = {fma(h, ba, aa), fma(h, bb, ab)};
+            v[n1] = {a[ca + L2 * n1], has_b ? a[cb + L2 * n1] : 0.0};
+            if constexpr (MODE != DK_THETA) {
+                const cd y = v[n1], g = {b[ca + L2 * n1], has_b ? b[cb + L2 * n1] : 0.0};
+                v[n1] = {fma(tau, g.re, y.re), fma(tau, g.im, y.im)};
+                keep[n1] = {fma(h, g.re, y.re), fma(h, g.im, y.im)};
             }
         });
-        transform<L1, -1>(v);
-        sfor<0, L1>([&](auto kc) {
-            constexpr int k1 = decltype(kc)::value;
-            cd w = v[k1];
-            if constexpr (k1 > 0) w = cmul(w, conj(tw[(n2 * k1) & (L - 1)]));
-            Y[k1 * S::RS + n2] = w;
-        });
     }
-    __syncthreads();
-    // Step 2 (thread k1 = lt): L2-point transforms over n2 give X[k1 + L1 k2]; multiply by
-    // i xi_m / L; inverse L2-point transforms; twiddle e^{+2 pi i n2 k1 / L}.
-    if (lt < L1 && has_a) {
-        const int k1 = lt;
-        cd v[L2];
-        sfor<0, L2>([&](auto ic) { v[decltype(ic)::value] = Y[k1 * S::RS + decltype(ic)::value]; });
-        transform<L2, -1>(v);
-        const double unit = 2.0 * kPi / (L * p.hk) / L;
-        sfor<0, L2>([&](auto kc) {
-            constexpr int k2 = decltype(kc)::value;
-            const int m = k1 + L1 * k2;
-            const double xi = m < L / 2 ? (double)m * unit : (m == L / 2 ? 0.0 : (double)(m - L) * unit);
-            v[k2] = {-xi * v[k2].im, xi * v[k2].re};
-        });
-        transform<L2, +1>(v);
-        sfor<0, L2>([&](auto nc) {
-            constexpr int n2 = decltype(nc)::value;
-            cd w = v[n2];
-            if constexpr (n2 > 0) w = cmul(w, tw[(n2 * k1) & (L - 1)]);
-            Y[k1 * S::RS + n2] = w;
-        });
+    derive(v);
+    if constexpr (MODE != DK_THETA) {
+        if (rows) {
+            sfor<0, L1>([&](auto ic) {
+                constexpr int n1 = decltype(ic)::value;
+                v[n1] = {fma(h, fa * v[n1].re, keep[n1].re), has_b ? fma(h, fb * v[n1].im, keep[n1].im) : 0.0};
+                out[ca + L2 * n1] = v[n1].re;
+                if (has_b) out[cb + L2 * n1] = v[n1].im;
+            });
+        }
     }
-    __syncthreads();
-    // Step 3 (thread n2 = lt): inverse L1-point transforms over k1 give d_k y at rows
-    // L2 n1 + n2; real part column xa, imaginary part column xb.
-    if (lt < L2 && has_a) {
-        const int n2 = lt;
-        cd v[L1];
-        sfor<0, L1>([&](auto kc) { v[decltype(kc)::value] = Y[decltype(kc)::value * S::RS + n2]; });
-        transform<L1, +1>(v);
-        const double fa = p.omega * (p.x_lo + xa * p.hx), fb = p.omega * (p.x_lo + xb * p.hx);
-        sfor<0, L1>([&](auto ic) {
-            constexpr int n1 = decltype(ic)::value;
-            const long long row = (long long)(L2 * n1 + n2) * p.nx;
-            if constexpr (MODE == 0) {
-                out[row + xa] = fa * v[n1].re;
-                if (has_b) out[row + xb] = fb * v[n1].im;
-            } else {
-                out[row + xa] = fma(h, fa * v[n1].re, keep[n1].re);
-                if (has_b) out[row + xb] = fma(h, fb * v[n1].im, keep[n1].im);
-            }
-        });
+    if constexpr (MODE == DK_STEP) {
+        __syncthreads();   // step 3 has read the rows that step 1 writes
+        derive(v);
+    }
+    if constexpr (MODE != DK_LAST) {
+        if (rows) {
+            sfor<0, L1>([&](auto ic) {
+                constexpr int n1 = decltype(ic)::value;
+                out2[ca + L2 * n1] = fa * v[n1].re;
+                if (has_b) out2[cb + L2 * n1] = fb * v[n1].im;
+            });
+        }
     }
 }
 
@@ -296,93 +421,105 @@ __global__ __launch_bounds__(64) void k_ho_dk(const double* __restrict__ a, cons
 //   step 2   (m1, n3): 8-point transform over n2, twiddle e^{-2 pi i 8 n3 m2 / 512}
 //   step 3   (m1, m2): 8-point transform over n3, times i xi_m / 512, inverse over m3
 //   steps 2', 1': the inverses of steps 2 and 1 with conjugate twiddles.
+// Thread (n2, n3) = (t / 8, t % 8) in step 1, so a wave's accesses are contiguous.
 template <int MODE>
 __global__ __launch_bounds__(64) void k_ho_dk512(const double* __restrict__ a, const double* __restrict__ b,
-                                                double* __restrict__ out, const fft::cd* __restrict__ tw,
-                                                const DkArgs p)
+                                                double* __restrict__ out, double* __restrict__ out2,
+                                                const fft::cd* __restrict__ tw, const DkArgs p)
 {
     using namespace fft;
-    constexpr int L = 512, RS = 65;                 // LDS rows of 64 values, padded
-    __shared__ cd S1[8 * RS];                        // [m1][n3][n2]
+    constexpr int L = 512, RS = 66;                 // LDS rows of 64 values, padded
+    __shared__ cd S1[8 * RS];                        // [m1][n2][n3]
     __shared__ cd S2[8 * RS];                        // [m1][m2][n3]
     const int t = threadIdx.x, lo = t & 7, hi = t >> 3;
     const int xa = 2 * blockIdx.x, xb = xa + 1;
     const bool has_b = xb < p.nx;
-    const double h = 0.5 * p.tau;
-    cd v[8];
-    cd keep[MODE == 1 ? 8 : 1];
-    // step 1: (n2, n3) = (lo, hi)
-    sfor<0, 8>([&](auto ic) {
-        constexpr int n1 = decltype(ic)::value;
-        const long long row = (long long)(64 * n1 + 8 * lo + hi) * p.nx;
-        if constexpr (MODE == 0) {
-            v[n1] = {a[row + xa], has_b ? a[row + xb] : 0.0};
-        } else {
-            const double aa = a[row + xa], ba = b[row + xa];
-            const double ab = has_b ? a[row + xb] : 0.0, bb = has_b ? b[row + xb] : 0.0;
-            v[n1] = {fma(p.tau, ba, aa), fma(p.tau, bb, ab)};
-            keep[n1] = {fma(h, ba, aa), fma(h, bb, ab)};
-        }
-    });
-    transform<8, -1>(v);
-    sfor<0, 8>([&](auto mc) {
-        constexpr int m1 = decltype(mc)::value;
-        cd w = v[m1];
-        if constexpr (m1 > 0) w = cmul(w, conj(tw[((8 * lo + hi) * m1) & (L - 1)]));
-        S1[m1 * RS + 8 * hi + lo] = w;
-    });
-    __syncthreads();
-    // step 2: (m1, n3) = (lo, hi)
-    sfor<0, 8>([&](auto ic) { v[decltype(ic)::value] = S1[lo * RS + 8 * hi + decltype(ic)::value]; });
-    transform<8, -1>(v);
-    sfor<0, 8>([&](auto mc) {
-        constexpr int m2 = decltype(mc)::value;
-        cd w = v[m2];
-        if constexpr (m2 > 0) w = cmul(w, conj(tw[(8 * hi * m2) & (L - 1)]));
-        S2[lo * RS + 8 * m2 + hi] = w;
-    });
-    __syncthreads();
-    // step 3: (m1, m2) = (lo, hi); the row is this thread's alone, read and written back
-    sfor<0, 8>([&](auto ic) { v[decltype(ic)::value] = S2[lo * RS + 8 * hi + decltype(ic)::value]; });
-    transform<8, -1>(v);
-    const double unit = 2.0 * kPi / (L * p.hk) / L;
-    sfor<0, 8>([&](auto mc) {
-        constexpr int m3 = decltype(mc)::value;
-        const int m = lo + 8 * hi + 64 * m3;
-        const double xi = m < L / 2 ? (double)m * unit : (m == L / 2 ? 0.0 : (double)(m - L) * unit);
-        v[m3] = {-xi * v[m3].im, xi * v[m3].re};
-    });
-    transform<8, +1>(v);
-    sfor<0, 8>([&](auto ic) { S2[lo * RS + 8 * hi + decltype(ic)::value] = v[decltype(ic)::value]; });
-    __syncthreads();
-    // step 2': (m1, n3) = (lo, hi)
-    sfor<0, 8>([&](auto mc) {
-        constexpr int m2 = decltype(mc)::value;
-        const cd x = S2[lo * RS + 8 * m2 + hi];
-        v[m2] = m2 > 0 ? cmul(x, tw[(8 * hi * m2) & (L - 1)]) : x;
-    });
-    transform<8, +1>(v);
-    sfor<0, 8>([&](auto ic) { S1[lo * RS + 8 * hi + decltype(ic)::value] = v[decltype(ic)::value]; });
-    __syncthreads();
-    // step 1': (n2, n3) = (lo, hi); d_k y at rows 64 n1 + 8 n2 + n3
-    sfor<0, 8>([&](auto mc) {
-        constexpr int m1 = decltype(mc)::value;
-        const cd x = S1[m1 * RS + 8 * hi + lo];
-        v[m1] = m1 > 0 ? cmul(x, tw[((8 * lo + hi) * m1) & (L - 1)]) : x;
-    });
-    transform<8, +1>(v);
+    const double h = 0.5 * p.tau, tau = p.tau, hk = p.hk;
     const double fa = p.omega * (p.x_lo + xa * p.hx), fb = p.omega * (p.x_lo + xb * p.hx);
+    const long long ca = (long long)xa * L + t, cb = (long long)xb * L + t;     // + 64 n1
+    // twiddles of this thread's elements, used forward (conjugated) and inverse
+    cd w1[8], w2[8];
+    sfor<1, 8>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        w1[m] = tw[(t * m) & (L - 1)];
+        w2[m] = tw[(8 * hi * m) & (L - 1)];
+    });
+
+    // v: elements 64 n1 + t of the column pair -> its k derivative at the same elements
+    auto derive = [&](cd (&v)[8]) {
+        // step 1: (n2, n3) = (hi, lo)
+        transform<8, -1>(v);
+        sfor<0, 8>([&](auto mc) {
+            constexpr int m1 = decltype(mc)::value;
+            S1[m1 * RS + t] = m1 > 0 ? cmul(v[m1], conj(w1[m1])) : v[m1];
+        });
+        __syncthreads();
+        // step 2: (m1, n3) = (lo, hi)
+        sfor<0, 8>([&](auto ic) { v[decltype(ic)::value] = S1[lo * RS + 8 * decltype(ic)::value + hi]; });
+        transform<8, -1>(v);
+        sfor<0, 8>([&](auto mc) {
+            constexpr int m2 = decltype(mc)::value;
+            S2[lo * RS + 8 * m2 + hi] = m2 > 0 ? cmul(v[m2], conj(w2[m2])) : v[m2];
+        });
+        __syncthreads();
+        // step 3: (m1, m2) = (lo, hi); the row is this thread's alone, read and written back
+        sfor<0, 8>([&](auto ic) { v[decltype(ic)::value] = S2[lo * RS + 8 * hi + decltype(ic)::value]; });
+        transform<8, -1>(v);
+        const double unit = 2.0 * kPi / (L * hk) / L;
+        sfor<0, 8>([&](auto mc) {
+            constexpr int m3 = decltype(mc)::value;
+            const int m = lo + 8 * hi + 64 * m3;
+            const double xi = m < L / 2 ? (double)m * unit : (m == L / 2 ? 0.0 : (double)(m - L) * unit);
+            v[m3] = {-xi * v[m3].im, xi * v[m3].re};
+        });
+        transform<8, +1>(v);
+        sfor<0, 8>([&](auto ic) { S2[lo * RS + 8 * hi + decltype(ic)::value] = v[decltype(ic)::value]; });
+        __syncthreads();
+        // step 2': (m1, n3) = (lo, hi)
+        sfor<0, 8>([&](auto mc) {
+            constexpr int m2 = decltype(mc)::value;
+            const cd x = S2[lo * RS + 8 * m2 + hi];
+            v[m2] = m2 > 0 ? cmul(x, w2[m2]) : x;
+        });
+        transform<8, +1>(v);
+        sfor<0, 8>([&](auto ic) { S1[lo * RS + 8 * decltype(ic)::value + hi] = v[decltype(ic)::value]; });
+        __syncthreads();
+        // step 1': (n2, n3) = (hi, lo); d_k y at elements 64 n1 + 8 n2 + n3
+        sfor<0, 8>([&](auto mc) {
+            constexpr int m1 = decltype(mc)::value;
+            const cd x = S1[m1 * RS + t];
+            v[m1] = m1 > 0 ? cmul(x, w1[m1]) : x;
+        });
+        transform<8, +1>(v);
+    };
+
+    cd v[8], keep[MODE == DK_THETA ? 1 : 8];
     sfor<0, 8>([&](auto ic) {
         constexpr int n1 = decltype(ic)::value;
-        const long long row = (long long)(64 * n1 + 8 * lo + hi) * p.nx;
-        if constexpr (MODE == 0) {
-            out[row + xa] = fa * v[n1].re;
-            if (has_b) out[row + xb] = fb * v[n1].im;
-        } else {
-            out[row + xa] = fma(h, fa * v[n1].re, keep[n1].re);
-            if (has_b) out[row + xb] = fma(h, fb * v[n1].im, keep[n1].im);
+        v[n1] = {a[ca + 64 * n1], has_b ? a[cb + 64 * n1] : 0.0};
+        if constexpr (MODE != DK_THETA) {
+            const cd y = v[n1], g = {b[ca + 64 * n1], has_b ? b[cb + 64 * n1] : 0.0};
+            v[n1] = {fma(tau, g.re, y.re), fma(tau, g.im, y.im)};
+            keep[n1] = {fma(h, g.re, y.re), fma(h, g.im, y.im)};
         }
     });
+    derive(v);
+    if constexpr (MODE != DK_THETA) {
+        sfor<0, 8>([&](auto ic) {
+            constexpr int n1 = decltype(ic)::value;
+            v[n1] = {fma(h, fa * v[n1].re, keep[n1].re), has_b ? fma(h, fb * v[n1].im, keep[n1].im) : 0.0};
+            out[ca + 64 * n1] = v[n1].re;
+            if (has_b) out[cb + 64 * n1] = v[n1].im;
+        });
+    }
+    if constexpr (MODE == DK_STEP) derive(v);   // step 1 writes S1 entries this thread alone has just read
+    if constexpr (MODE != DK_LAST) {
+        sfor<0, 8>([&](auto ic) {
+            constexpr int n1 = decltype(ic)::value;
+            out2[ca + 64 * n1] = fa * v[n1].re;
+            if (has_b) out2[cb + 64 * n1] = fb * v[n1].im;
+        });
+    }
 }
 
 // mode 0: dst = a + c b;  mode 1: dst = a + c (b + y)
@@ -392,38 +529,6 @@ __global__ __launch_bounds__(256) void k_ho_combine(double* __restrict__ dst, co
 {
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256)
         dst[i] = mode == 0 ? fma(c, b[i], a[i]) : fma(c, b[i] + y[i], a[i]);
-}
-
-// Inverse of the (m+1) x (m+1) reduced patch matrix [4 2; 1 4 1; ...; 2 4] (the Hermite
-// rows of eq. 2.13 eliminated into the interpolation rows of eq. 2.12, times 6), by
-// Gauss-Jordan elimination (diagonally dominant: no pivoting needed).
-static std::vector<double> patch_inverse(int m)
-{
-    const int n = m + 1;
-    std::vector<double> A((size_t)n * n, 0.0), I((size_t)n * n, 0.0);
-    for (int i = 0; i < n; ++i) {
-        A[(size_t)i * n + i] = 4.0;
-        if (i > 0) A[(size_t)i * n + i - 1] = i == n - 1 ? 2.0 : 1.0;
-        if (i < n - 1) A[(size_t)i * n + i + 1] = i == 0 ? 2.0 : 1.0;
-        I[(size_t)i * n + i] = 1.0;
-    }
-    for (int k = 0; k < n; ++k) {
-        const double p = A[(size_t)k * n + k];
-        for (int j = 0; j < n; ++j) {
-            A[(size_t)k * n + j] /= p;
-            I[(size_t)k * n + j] /= p;
-        }
-        for (int r = 0; r < n; ++r) {
-            if (r == k) continue;
-            const double f = A[(size_t)r * n + k];
-            if (f == 0.0) continue;
-            for (int j = 0; j < n; ++j) {
-                A[(size_t)r * n + j] -= f * A[(size_t)k * n + j];
-                I[(size_t)r * n + j] -= f * I[(size_t)k * n + j];
-            }
-        }
-    }
-    return I;
 }
 
 // Spectral differentiation on the periodic grid of n (even) points, spacing h:
@@ -465,35 +570,44 @@ static chasm_status hfail(chasm_status st, const std::string& m)
 static bool dk_by_transform(int nk) { return nk >= 64 && nk <= 1024 && (nk & (nk - 1)) == 0; }
 
 template <int L1, int L2>
-static void launch_dk_t(int mode, const double* a, const double* b, double* out, const fft::cd* tw, const DkArgs& p,
-                        hipStream_t s)
+static void launch_dk_t(int mode, const double* a, const double* b, double* out, double* out2, const fft::cd* tw,
+                        const DkArgs& p, hipStream_t s)
 {
     using S = DkShape<L1, L2>;
     const int ncl = (p.nx + 1) / 2;
     const dim3 grid((unsigned)((ncl + S::CLB - 1) / S::CLB));
-    if (mode == 0)
-        hipLaunchKernelGGL((k_ho_dk<L1, L2, 0>), grid, dim3(S::NT), 0, s, a, b, out, tw, p);
-    else
-        hipLaunchKernelGGL((k_ho_dk<L1, L2, 1>), grid, dim3(S::NT), 0, s, a, b, out, tw, p);
+    auto k = mode == DK_THETA ? k_ho_dk<L1, L2, DK_THETA> : mode == DK_LAST ? k_ho_dk<L1, L2, DK_LAST> : k_ho_dk<L1, L2, DK_STEP>;
+    hipLaunchKernelGGL(k, grid, dim3(S::NT), 0, s, a, b, out, out2, tw, p);
 }
 
-static void launch_dk(int nk, int mode, const double* a, const double* b, double* out, const fft::cd* tw,
+static void launch_dk(int nk, int mode, const double* a, const double* b, double* out, double* out2, const fft::cd* tw,
                       const DkArgs& p, hipStream_t s)
 {
     switch (nk) {
-    case 64: launch_dk_t<8, 8>(mode, a, b, out, tw, p, s); break;
-    case 128: launch_dk_t<8, 16>(mode, a, b, out, tw, p, s); break;
-    case 256: launch_dk_t<16, 16>(mode, a, b, out, tw, p, s); break;
+    case 64: launch_dk_t<8, 8>(mode, a, b, out, out2, tw, p, s); break;
+    case 128: launch_dk_t<8, 16>(mode, a, b, out, out2, tw, p, s); break;
+    case 256: launch_dk_t<16, 16>(mode, a, b, out, out2, tw, p, s); break;
     case 512: {
-        const dim3 grid((unsigned)((p.nx + 1) / 2));
-        if (mode == 0)
-            hipLaunchKernelGGL(k_ho_dk512<0>, grid, dim3(64), 0, s, a, b, out, tw, p);
-        else
-            hipLaunchKernelGGL(k_ho_dk512<1>, grid, dim3(64), 0, s, a, b, out, tw, p);
+        auto k = mode == DK_THETA ? k_ho_dk512<DK_THETA> : mode == DK_LAST ? k_ho_dk512<DK_LAST> : k_ho_dk512<DK_STEP>;
+        hipLaunchKernelGGL(k, dim3((unsigned)((p.nx + 1) / 2)), dim3(64), 0, s, a, b, out, out2, tw, p);
         break;
     }
-    default: launch_dk_t<32, 32>(mode, a, b, out, tw, p, s); break;
+    default: launch_dk_t<32, 32>(mode, a, b, out, out2, tw, p, s); break;
     }
+}
+
+// Four lines per block where they fit in 64 KB of LDS (256 blocks at nk = 512), else two
+// (every accepted line fits: see the limit in chasm_ho2d_create).
+template <bool XK>
+static void launch_advect(const double* in, double* out, const HoArgs& a, hipStream_t s)
+{
+    const int nlines = 2 * a.nk;
+    const size_t lds4 = (4 * (size_t)ho_line_doubles(4, a.N, a.P) + 3 * HO_LU) * sizeof(double);
+    const size_t lds2 = 2 * (size_t)ho_line_doubles(2, a.N, a.P) * sizeof(double);
+    if (lds4 <= 65536)
+        hipLaunchKernelGGL((k_ho_advect<4, XK>), dim3((unsigned)((nlines + 3) / 4)), dim3(256), lds4, s, in, out, a, nlines);
+    else
+        hipLaunchKernelGGL((k_ho_advect<2, XK>), dim3((unsigned)((nlines + 1) / 2)), dim3(256), lds2, s, in, out, a, nlines);
 }
 
 extern "C" {
@@ -519,10 +633,15 @@ chasm_status chasm_ho2d_create(const chasm_ho2d_desc* d, void* f_dev, void* hip_
     if (!build_axis_tables(d->nx, d->patch, d->ghost, d->ghost, d->hx, 0, d->nk, d->k_lo, d->hk, d->tau, at, err))
         return hfail(CHASM_EINVAL, err);
     const int P = at.P, M = d->patch, mlast = at.MLAST;
-    if ((size_t)HO_LB * (2 * d->nx + 4 * P) * sizeof(double) > 65536)
+    if ((size_t)2 * (2 * d->nx + 4 * P) * sizeof(double) > 65536)
         return hfail(CHASM_EINVAL, "lines too long for the LDS line kernel (2 lines of 2 nx + 4 P doubles <= 64 KiB)");
     const bool by_transform = dk_by_transform(d->nk);
-    const std::vector<double> AM = patch_inverse(M), AL = patch_inverse(mlast);
+    std::vector<double> LU((size_t)3 * (HO_LU + 1)), LM((size_t)3 * (M + 1)), LL((size_t)3 * (mlast + 1));
+    patch_factors(HO_LU, LU.data(), LU.data() + (HO_LU + 1), LU.data() + 2 * (HO_LU + 1));
+    for (int i = 1; i < 3; ++i) std::copy_n(LU.begin() + i * (HO_LU + 1), HO_LU, LU.begin() + i * HO_LU);
+    LU.resize((size_t)3 * HO_LU);
+    patch_factors(M, LM.data(), LM.data() + (M + 1), LM.data() + 2 * (M + 1));
+    patch_factors(mlast, LL.data(), LL.data() + (mlast + 1), LL.data() + 2 * (mlast + 1));
     const std::vector<double> D = by_transform ? std::vector<double>() : spectral_dk(d->nk, d->hk);
     std::vector<fft::cd> TW;
     if (by_transform)
@@ -538,14 +657,13 @@ chasm_status chasm_ho2d_create(const chasm_ho2d_desc* d, void* f_dev, void* hip_
         chasm_ho2d_destroy(h);
         return hfail(s, m);
     };
-    // one block: stencil | ainvM | ainvL | w (doubles), then shift (ints)
-    const size_t nd = at.stencil.size() + AM.size() + AL.size() + at.w.size();
+    // one block: stencil | patch factors | w (doubles), then shift (ints)
+    const size_t nd = at.stencil.size() + LU.size() + at.w.size();
     std::vector<char> blob(nd * sizeof(double) + at.shift.size() * sizeof(int));
     double* dp = reinterpret_cast<double*>(blob.data());
     size_t o = 0;
     const size_t o_st = o; std::copy(at.stencil.begin(), at.stencil.end(), dp + o); o += at.stencil.size();
-    const size_t o_am = o; std::copy(AM.begin(), AM.end(), dp + o); o += AM.size();
-    const size_t o_al = o; std::copy(AL.begin(), AL.end(), dp + o); o += AL.size();
+    const size_t o_lu = o; std::copy(LU.begin(), LU.end(), dp + o); o += LU.size();
     const size_t o_w = o; std::copy(at.w.begin(), at.w.end(), dp + o); o += at.w.size();
     std::copy(at.shift.begin(), at.shift.end(), reinterpret_cast<int*>(dp + o));
     if (hipMalloc(&h->tables, blob.size()) != hipSuccess) return bail(CHASM_ENOMEM, "hipMalloc(tables) failed");
@@ -575,8 +693,11 @@ chasm_status chasm_ho2d_create(const chasm_ho2d_desc* d, void* f_dev, void* hip_
     a.inflow = d->inflow;
     a.hx = d->hx;
     a.stencil = tb + o_st;
-    a.ainvM = tb + o_am;
-    a.ainvL = tb + o_al;
+    a.lu = tb + o_lu;
+    a.inv_l[0] = LM[M];
+    a.ainv_l[0] = LM[2 * M + 1];
+    a.inv_l[1] = LL[mlast];
+    a.ainv_l[1] = LL[2 * mlast + 1];
     a.w = tb + o_w;
     a.shift = reinterpret_cast<const int*>(tb + o);
     *out = h;
@@ -594,31 +715,39 @@ chasm_status chasm_ho2d_step(chasm_ho2d_t h, int32_t nsteps)
     const long long n = h->n;
     const size_t fb = (size_t)n * sizeof(double);
     hipStream_t s = h->stream;
-    const int nlines = 2 * d.nk;
-    const size_t smem = (size_t)HO_LB * (2 * a.N + 4 * a.P) * sizeof(double);
-    const dim3 tgrid((unsigned)((d.nx + 31) / 32), (unsigned)((d.nk + 31) / 32));
-    const unsigned cgrid = (unsigned)std::min<long long>((n + 255) / 256, 4096);
     double *F = h->X, *G = h->X + n, *FA = h->XA, *GA = h->XA + n;
-    hipError_t e = hipMemcpyAsync(F, h->f, fb, hipMemcpyDeviceToDevice, s);
-    const DkArgs dp{d.nx, d.x_lo, d.hx, d.hk, d.omega, d.tau};
-    for (int it = 0; it < nsteps && e == hipSuccess && h->tw; ++it) {
-        // predictor Theta F; advect (F, Theta F); corrector fused with Theta (FA + tau GA)
-        launch_dk(d.nk, 0, F, nullptr, G, h->tw, dp, s);
-        hipLaunchKernelGGL(k_ho_advect, dim3((unsigned)((nlines + HO_LB - 1) / HO_LB)), dim3(256), smem, s, h->X, h->XA,
-                           a, nlines);
-        launch_dk(d.nk, 1, FA, GA, F, h->tw, dp, s);
+    hipError_t e = hipSuccess;
+    if (h->tw) {
+        // Theta F; then per step: advect (F, Theta F); corrector fused with Theta (FA + tau
+        // GA) and, but for the last step, with the next step's Theta F
+        const DkArgs dp{d.nx, d.x_lo, d.hx, d.hk, d.omega, d.tau};
+        const dim3 to((unsigned)((d.nx + 31) / 32), (unsigned)((d.nk + 31) / 32)), from(to.y, to.x);
+        hipLaunchKernelGGL(k_ho_turn, to, dim3(256), 0, s, h->f, F, d.nk, d.nx);
+        launch_dk(d.nk, DK_THETA, F, nullptr, nullptr, G, h->tw, dp, s);
         e = hipGetLastError();
+        for (int it = 0; it < nsteps && e == hipSuccess; ++it) {
+            launch_advect<true>(h->X, h->XA, a, s);
+            launch_dk(d.nk, it + 1 < nsteps ? DK_STEP : DK_LAST, FA, GA, F, G, h->tw, dp, s);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(k_ho_turn, from, dim3(256), 0, s, F, h->f, d.nx, d.nk);
+            e = hipGetLastError();
+        }
+    } else {
+        const dim3 tgrid((unsigned)((d.nx + 31) / 32), (unsigned)((d.nk + 31) / 32));
+        const unsigned cgrid = (unsigned)std::min<long long>((n + 255) / 256, 4096);
+        e = hipMemcpyAsync(F, h->f, fb, hipMemcpyDeviceToDevice, s);
+        for (int it = 0; it < nsteps && e == hipSuccess; ++it) {
+            hipLaunchKernelGGL(k_ho_theta, tgrid, dim3(256), 0, s, h->D, F, G, d.nk, d.nx, d.x_lo, d.hx, d.omega);
+            launch_advect<false>(h->X, h->XA, a, s);
+            hipLaunchKernelGGL(k_ho_combine, dim3(cgrid), dim3(256), 0, s, h->Y, FA, GA, (const double*)nullptr, n, d.tau, 0);
+            hipLaunchKernelGGL(k_ho_theta, tgrid, dim3(256), 0, s, h->D, h->Y, h->Z, d.nk, d.nx, d.x_lo, d.hx, d.omega);
+            hipLaunchKernelGGL(k_ho_combine, dim3(cgrid), dim3(256), 0, s, F, FA, GA, h->Z, n, 0.5 * d.tau, 1);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipMemcpyAsync(h->f, F, fb, hipMemcpyDeviceToDevice, s);
     }
-    for (int it = 0; it < nsteps && e == hipSuccess && !h->tw; ++it) {
-        hipLaunchKernelGGL(k_ho_theta, tgrid, dim3(256), 0, s, h->D, F, G, d.nk, d.nx, d.x_lo, d.hx, d.omega);
-        hipLaunchKernelGGL(k_ho_advect, dim3((unsigned)((nlines + HO_LB - 1) / HO_LB)), dim3(256), smem, s, h->X, h->XA,
-                           a, nlines);
-        hipLaunchKernelGGL(k_ho_combine, dim3(cgrid), dim3(256), 0, s, h->Y, FA, GA, (const double*)nullptr, n, d.tau, 0);
-        hipLaunchKernelGGL(k_ho_theta, tgrid, dim3(256), 0, s, h->D, h->Y, h->Z, d.nk, d.nx, d.x_lo, d.hx, d.omega);
-        hipLaunchKernelGGL(k_ho_combine, dim3(cgrid), dim3(256), 0, s, F, FA, GA, h->Z, n, 0.5 * d.tau, 1);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpyAsync(h->f, F, fb, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) {
         h->poisoned = true;
         return hfail(CHASM_EDEVICE, std::string("ho2d step: ") + hipGetErrorString(e));

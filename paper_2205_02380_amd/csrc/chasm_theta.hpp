@@ -64,6 +64,29 @@ __device__ __forceinline__ void load_k1(const T* __restrict__ p, double (&v)[NK]
     }
 }
 
+// The same without the conversion.
+template <typename T, int NK>
+__device__ __forceinline__ void load_raw(const T* __restrict__ p, T (&v)[NK])
+{
+    using V = typename std::conditional<sizeof(T) == 4, float4, double2>::type;
+    constexpr int n = sizeof(V) / sizeof(T);
+    static_assert(NK % n == 0, "whole vectors");
+    const V* q = reinterpret_cast<const V*>(p);
+    fft::sfor<0, NK / n>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const V t = q[i];
+        if constexpr (n == 4) {
+            v[4 * i] = t.x;
+            v[4 * i + 1] = t.y;
+            v[4 * i + 2] = t.z;
+            v[4 * i + 3] = t.w;
+        } else {
+            v[2 * i] = t.x;
+            v[2 * i + 1] = t.y;
+        }
+    });
+}
+
 template <typename T, int NK>
 __device__ __forceinline__ void store_k1(T* __restrict__ p, const double (&v)[NK])
 {

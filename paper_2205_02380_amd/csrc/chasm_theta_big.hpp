@@ -17,7 +17,7 @@
 // h < S = P / 32, is a 32-point transform of the twiddled line folded modulo 32, so
 // each work item of A and E holds 32 complex values in registers.  The field is in x-major
 // order [b][x][k3][k2][k1], as for k_theta.  The modulations are per-axis factors of the
-// handle's table: k1 and k3 in A and E (one product table per block), k2 in k_thBCD.
+// handle's table: k1 and k3 in A and E, k2 in k_thBCD.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -39,18 +39,28 @@ struct BigShape {
     static_assert(P % L == 0 && NK * NK % LA == 0 && LE % NK == 0, "shape");
 };
 
-// The factors that A and E apply along k1 on the block's KR rows k3 = r0 .. r0 + KR - 1:
-// e02[h][kr][j] = e^{-i phi_1 j} w^{h j} e^{-i phi_3 k3} (the k2 factor rides on the
-// twiddles of B and D).
-template <int NK, int KR>
-__device__ __forceinline__ void big_factors(fft::cd (*e02)[KR][NK], const fft::cd* et, const ModRows& e, int r0)
+// The factors that A and E apply along k1 on this thread's line (row k3): entry j =
+// e^{-i phi_1 j} e^{-i phi_3 k3} (the k2 factor rides on the twiddles of B and D), for
+// residue h = 0, times wgt; next_residue multiplies by w^j.
+template <int NK>
+__device__ __forceinline__ LineFactors<NK> big_factors(const ModRows& e, int k3, double wgt = 1.0)
 {
-    using namespace fft;
-    constexpr int S = BigShape<NK>::S;
-    for (int t = threadIdx.x; t < S * KR * NK; t += blockDim.x) {
-        const int j = t % NK, kr = (t / NK) % KR, h = t / (NK * KR);
-        e02[h][kr][j] = cmul(cmul(e.e1[j], et[(h * j) % (2 * NK)]), e.e3[r0 + kr]);
-    }
+    LineFactors<NK> f;
+    const fft::cd e3 = {wgt * e.e3[k3].re, wgt * e.e3[k3].im};
+    fft::sfor<0, NK / 16>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        f.v[q] = fft::cmul(e.e1[threadIdx.x % 16 + 16 * q], e3);
+    });
+    return f;
+}
+
+template <int NK>
+__device__ __forceinline__ void next_residue(LineFactors<NK>& f, const fft::cd* et)
+{
+    fft::sfor<0, NK / 16>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        f.v[q] = fft::cmul(f.v[q], et[threadIdx.x % 16 + 16 * q]);
+    });
 }
 
 // ---- A: k1 forward.  Block = 256 k1 lines of one x-point, a thread per line and one
@@ -62,13 +72,10 @@ __global__ __launch_bounds__(BigShape<NK>::LA, 2) void k_thA(const T* __restrict
 {
     using namespace fft;
     using B = BigShape<NK>;
-    constexpr int P = B::P, S = B::S, KR = B::LA / NK, BPX = NK * NK / B::LA;
-    __shared__ cd E02[S][KR][NK];
+    constexpr int P = B::P, S = B::S, BPX = NK * NK / B::LA;
     const long long xl = blockIdx.x / BPX;
     const int l0 = (int)(blockIdx.x % BPX) * B::LA, la = l0 + threadIdx.x;   // k3 * NK + k2
-    const int kr = threadIdx.x / NK;
-    big_factors<NK, KR>(E02, et, mod_rows_at<NK>(et, a, x0 + xl, nu), l0 / NK);
-    __syncthreads();
+    LineFactors<NK> lf = big_factors<NK>(mod_rows_at<NK>(et, a, x0 + xl, nu), la / NK);
     const T* line = fx + (x0 + xl) * (long long)(NK * NK * NK) + (long long)la * NK;
     cd* out = W + xl * (long long)(P * NK * NK) + la;
 #pragma unroll 1
@@ -81,7 +88,7 @@ __global__ __launch_bounds__(BigShape<NK>::LA, 2) void k_thA(const T* __restrict
             load_k1<T, n>(line + k0, fv);
             sfor<0, n>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
-                const cd m = E02[h][kr][k0 + k];
+                const cd m = lf.template at<k0 + k>();
                 if constexpr (k0 == 0) y[k] = cd{m.re * fv[k], m.im * fv[k]};
                 else y[k] = cd{fma(m.re, fv[k], y[k].re), fma(m.im, fv[k], y[k].im)};
             });
@@ -92,14 +99,15 @@ __global__ __launch_bounds__(BigShape<NK>::LA, 2) void k_thA(const T* __restrict
             constexpr int f = decltype(fc)::value;
             out[(long long)(S * f + h) * (NK * NK)] = y[f];   // xi1 = S f + h
         });
+        next_residue<NK>(lf, et);
     }
 }
 
 // ---- B, C, D for N_k <= 32: planes W[x][xi1][k3][k2] through plane_conv, in place; a
 // one-wave block takes 64 / (2 N_k) planes, and no lane waits for another wave.  At
-// N_k = 32 a lane's half line (32 complex values) and the Toeplitz sums fill 254 VGPRs: two
-// waves per SIMD, FP64 VALU bound.  Per 2048 x-points: 1.60 ms, against 2.26 ms for one
-// wave per SIMD with half the lanes idle in B and D; k_thA 0.42 (0.61), k_thE 0.57 (0.87).
+// N_k = 32 a lane's half line (32 complex values) and the Toeplitz sums fill 256 VGPRs: two
+// waves per SIMD, FP64 VALU bound.  Per 2048 x-points: 1.38 ms, against 2.26 ms for one
+// wave per SIMD with half the lanes idle in B and D; k_thA 0.43 (0.61), k_thE 0.58 (0.87).
 template <int NK>
 __global__ __launch_bounds__(64, 2) void k_thBCD_plane(fft::cd* __restrict__ W, const double* __restrict__ kt,
                                                       const fft::cd* __restrict__ et, const ThetaArgs a,
@@ -109,26 +117,19 @@ __global__ __launch_bounds__(64, 2) void k_thBCD_plane(fft::cd* __restrict__ W, 
     using S = PlaneShape<NK>;
     constexpr int P = S::P, RS = S::RS, PPB = 64 / S::LANES;
     __shared__ cd slots[PPB * S::SLOT];
-    __shared__ cd TWF[2][NK], TWD[2][NK];
     const int lane = threadIdx.x % S::LANES, k3 = lane % NK, h = lane / NK, grp = threadIdx.x / S::LANES;
     const long long p = (long long)blockIdx.x * PPB + grp;
     const int xi1 = (int)(p % P);
     cd* plane = W + p * (long long)(NK * NK);
     cd* slot = slots + grp * S::SLOT;
     // a block's planes belong to one x-point (PPB divides P)
-    const cd* e2 = mod_rows_at<NK>(et, a, x0 + p / P, nu).e2;
-    if (threadIdx.x < 2 * NK) {
-        const int hh = threadIdx.x / NK, j = threadIdx.x % NK;
-        const cd f = hh ? cmul(e2[j], et[j]) : e2[j];
-        TWF[hh][j] = f;
-        TWD[hh][j] = cd{a.wgt[nu] * f.re, -a.wgt[nu] * f.im};
-    }
+    LineFactors<NK> tw = half_factors<NK>(et, mod_rows_at<NK>(et, a, x0 + p / P, nu).e2, h, lane, nullptr);
     sfor<0, NK / 2>([&](auto ic) {   // two rows per step
         constexpr int i = decltype(ic)::value;
         slot[(2 * i + h) * RS + k3] = plane[2 * i * NK + lane];
     });
     __syncthreads();
-    plane_conv<NK>(slot, kt + ((long long)xi1 * P + 2 * k3 + h) * NK, TWF[h], TWD[h], k3, h);
+    plane_conv<NK>(slot, kt + ((long long)xi1 * P + 2 * k3 + h) * NK, tw, k3, h);
     __syncthreads();
     sfor<0, NK / 2>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
@@ -155,7 +156,6 @@ __global__ __launch_bounds__(BigShape<NK>::NTB) void k_thBCD(fft::cd* __restrict
     const int xi1 = (int)(blockIdx.x % P);
     cd* slice = W + (xl * P + xi1) * (long long)(NK * NK);
     const int tid = threadIdx.x;
-    const double wgt = a.wgt[nu];
     const cd* e2 = mod_rows_at<NK>(et, a, x0 + xl, nu).e2;
     for (int t = tid; t < S * NK; t += NT) TW[t / NK][t % NK] = cmul(e2[t % NK], et[((t / NK) * (t % NK)) % P]);
     __syncthreads();
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(BigShape<NK>::NTB) void k_thBCD(fft::cd* __restrict
             transform<32, +1>(v);
             sfor<0, NK>([&](auto jc) {
                 constexpr int j2 = decltype(jc)::value;
-                const cd x = cmul(v[j2 % 32], cd{wgt * TW[h][j2].re, -wgt * TW[h][j2].im});
+                const cd x = cmul(v[j2 % 32], conj(TW[h][j2]));
                 ACC[j3 * RS + j2] = h == 0 ? x : cadd(ACC[j3 * RS + j2], x);
             });
         }
@@ -244,15 +244,12 @@ __global__ __launch_bounds__(BigShape<NK>::LE, 2) void k_thE(const fft::cd* __re
 {
     using namespace fft;
     using B = BigShape<NK>;
-    constexpr int P = B::P, S = B::S, RS = B::RS, KR = B::LE / NK, BPX = NK * NK / B::LE;
+    constexpr int P = B::P, S = B::S, RS = B::RS, BPX = NK * NK / B::LE;
     constexpr bool REG = NK <= 32;
-    __shared__ cd E02[S][KR][NK];
     __shared__ double TH[REG ? 1 : B::LE * RS];
     const long long xl = blockIdx.x / BPX;
     const int l0 = (int)(blockIdx.x % BPX) * B::LE, la = l0 + threadIdx.x;   // j3 * NK + j2
-    const int kr = threadIdx.x / NK;
-    big_factors<NK, KR>(E02, et, mod_rows_at<NK>(et, a, x0 + xl, nu), l0 / NK);
-    __syncthreads();
+    LineFactors<NK> lf = big_factors<NK>(mod_rows_at<NK>(et, a, x0 + xl, nu), la / NK, a.wgt[nu]);
     const cd* src = W + xl * (long long)(P * NK * NK) + la;
     const long long off = (x0 + xl) * (long long)(NK * NK * NK) + (long long)la * NK;
     double* ac = acc + xl * (long long)(NK * NK * NK) + (long long)la * NK;
@@ -273,9 +270,10 @@ __global__ __launch_bounds__(BigShape<NK>::LE, 2) void k_thE(const fft::cd* __re
         transform<32, +1>(v);
         sfor<0, NK>([&](auto jc) {
             constexpr int j1 = decltype(jc)::value;
-            const cd m = E02[h][kr][j1];
+            const cd m = lf.template at<j1>();
             at(jc) = fma(m.re, v[j1 % 32].im, fma(-m.im, v[j1 % 32].re, at(jc)));   // Im(conj(m) v)
         });
+        next_residue<NK>(lf, et);
     }
     if (last) {
         sfor<0, (NK + 31) / 32>([&](auto sc) {

@@ -15,8 +15,9 @@
 // imaginary parts (K is real, so the two parts of C are independent), 2 N_k lines of
 // N_k doubles -- exactly the slot's size.  The sum over h exchanges half of each line
 // with the partner lane, after which each lane holds N_k/2 outputs of its row.
-// Twiddles that a lane needs for its own h come from LDS with the modulation along k2
-// folded in.
+// The factors that a lane needs for its own h (twiddles with the modulation along k2
+// folded in) are held one or two to a lane and broadcast within rows of 16 lanes
+// (LineFactors).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -68,12 +69,49 @@ __device__ __forceinline__ double pair_sum(double a, double b, int h)
     }
 }
 
-// o = K x for the symmetric Toeplitz matrix K[j][i] = kk[|j - i|], sixteen outputs at a
-// time (bounds the accumulators at N_k = 32).
+// x of lane N of this lane's row of 16 lanes (a DPP move, no LDS).
+template <int N>
+__device__ __forceinline__ double row_bcast(double x)
+{
+    return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + N, 0xF, 0xF, true);
+}
+
+// The N_k complex factors of a line, the same for all lanes of a row of 16: lane l holds
+// entries l % 16 + 16 q and every use broadcasts one (two moves; an LDS table costs a
+// 16-byte read of every lane).  N_k = 8 has two lines to a row of 16 lanes and reads an
+// LDS table.
+template <int NK>
+struct LineFactors {
+    fft::cd v[NK / 16];
+    template <int J>
+    __device__ __forceinline__ fft::cd at() const
+    {
+        return {row_bcast<J % 16>(v[J / 16].re), row_bcast<J % 16>(v[J / 16].im)};
+    }
+    // Between two uses of the line: the broadcasts of the first are not kept for the second
+    // (64 registers at N_k = 16).
+    __device__ __forceinline__ void renew()
+    {
+        fft::sfor<0, NK / 16>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            asm volatile("" : "+v"(v[q].re), "+v"(v[q].im));
+        });
+    }
+};
+template <>
+struct LineFactors<8> {
+    const fft::cd* v;
+    template <int J>
+    __device__ __forceinline__ fft::cd at() const { return v[J]; }
+    __device__ __forceinline__ void renew() {}
+};
+
+// o = K x for the symmetric Toeplitz matrix K[j][i] = kk[|j - i|], JB outputs at a time
+// (bounds the accumulators).
 template <int NK>
 __device__ __forceinline__ void toeplitz_line(const double (&kk)[NK], double* line)
 {
-    constexpr int JB = NK < 16 ? NK : 16;
+    constexpr int JB = 8;
     double x[NK];
     fft::sfor<0, NK>([&](auto ic) { x[decltype(ic)::value] = line[decltype(ic)::value]; });
     fft::sfor<0, NK / JB>([&](auto bc) {
@@ -93,15 +131,19 @@ __device__ __forceinline__ void toeplitz_line(const double (&kk)[NK], double* li
 }
 
 // Stages B, C, D of the plane in `slot`, in place.  k3, h: this lane's row and half;
-// kt: the kernel values K(xi1, 2 k3 + h, 0 .. N_k - 1) of this lane's line; twf, twd: the
-// factors of this lane's half, row_j -> row_j twf_j before B and out_j -> out_j twd_j
-// after D.
+// kt: the kernel values K(xi1, 2 k3 + h, 0 .. N_k - 1) of this lane's line; tw: the factors
+// of this lane's half, row_j -> row_j tw_j before B and out_j -> conj(tw_j) out_j after D.
 template <int NK>
-__device__ __forceinline__ void plane_conv(fft::cd* slot, const double* __restrict__ kt, const fft::cd* twf,
-                                           const fft::cd* twd, int k3, int h)
+__device__ __forceinline__ void plane_conv(fft::cd* slot, const double* __restrict__ kt, LineFactors<NK>& tw, int k3,
+                                           int h)
 {
     using namespace fft;
     using S = PlaneShape<NK>;
+    // the plane's row and the kernel values are all requested before the first use of any
+    // (left to itself the compiler reads the row one value at a time)
+    cd y[NK];
+    cd* row = slot + k3 * S::RS;
+    sfor<0, NK>([&](auto jc) { y[decltype(jc)::value] = row[decltype(jc)::value]; });
     double kk[NK];
     const double2* kr = reinterpret_cast<const double2*>(kt);
     sfor<0, NK / 2>([&](auto qc) {
@@ -110,12 +152,12 @@ __device__ __forceinline__ void plane_conv(fft::cd* slot, const double* __restri
         kk[2 * q] = t.x;
         kk[2 * q + 1] = t.y;
     });
-    cd y[NK];
-    cd* row = slot + k3 * S::RS;
+    __builtin_amdgcn_sched_barrier(0);
     sfor<0, NK>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        y[j] = cmul(row[j], twf[j]);
+        y[j] = cmul(y[j], tw.template at<j>());
     });
+    tw.renew();
     transform<NK, -1>(y);
     wave_order();
     double* col = reinterpret_cast<double*>(slot) + h * NK * S::RS + k3;      // row k3 of half h: stride RS
@@ -133,9 +175,10 @@ __device__ __forceinline__ void plane_conv(fft::cd* slot, const double* __restri
     sfor<0, NK>([&](auto fc) { y[decltype(fc)::value].im = col[decltype(fc)::value * S::RS]; });
     wave_order();
     transform<NK, +1>(y);
+    tw.renew();
     sfor<0, NK>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        y[j] = cmul(y[j], twd[j]);
+        y[j] = cmul(y[j], conj(tw.template at<j>()));
     });
     constexpr int H = NK / 2;
     sfor<0, H>([&](auto jc) {
@@ -185,98 +228,134 @@ __device__ __forceinline__ ModRows mod_rows_at(const fft::cd* et, const ThetaArg
     return {e + i1 * NK, e + (a.nx[0] + i2) * NK, e + (a.nx[0] + a.nx[1] + i3) * NK};
 }
 
+// Factors of a half line: entry j = e2_j w^{h j}, as LineFactors for lane `lane` of the
+// block (lds: N_k = 8 only, the table [h][j] with rows of 9, written by this call).
+template <int NK>
+__device__ __forceinline__ LineFactors<NK> half_factors(const fft::cd* et, const fft::cd* e2, int h, int lane, fft::cd* lds)
+{
+    using namespace fft;
+    if constexpr (NK == 8) {
+        const int hh = (lane / 8) & 1, j = lane % 8;
+        lds[hh * 9 + j] = hh ? cmul(e2[j], et[j]) : e2[j];
+        return {lds + h * 9};
+    } else {
+        LineFactors<NK> f;
+        sfor<0, NK / 16>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            const int j = lane % 16 + 16 * q;
+            f.v[q] = h ? cmul(e2[j], et[j]) : e2[j];
+        });
+        return f;
+    }
+}
+
 // One x-point per block at a time (persistent over x-points), N_k^2 threads, FP64
-// throughout.  The xi1 axis goes by parity: chunk r holds xi1 = r + 2 m (m < N_k), the
-// N_k-point transform of line_j e^{-i phi_1 j} w^{r j}.  Per chunk:
-//   A  thread (k2, k3): modulated k1 line, N_k-point transform      -> plane m, [k3][k2]
-//   BCD  plane_conv on the N_k planes, 2 N_k lanes each
-//   E  thread (k2, k3): N_k-point inverse over the planes, demodulated, into the real
+// throughout.  The xi1 axis goes by residue: chunk r < R holds xi1 = r + R m, m < C = 8
+// (R C = P), the C-point transform of line_j e^{-i phi_1 j} w^{r j} folded modulo C.  Per
+// chunk:
+//   A  thread (k2, k3): modulated k1 line, C-point transform        -> plane m, [k3][k2]
+//   BCD  plane_conv on the C planes, 2 N_k lanes each
+//   E  thread (k2, k3): C-point inverse over the planes, demodulated, into the real
 //      result the thread keeps in registers (16 doubles at N_k = 16)
-// The modulations are products of per-axis factors: e02 = e^{-i phi_1 j} w^{r j}
-// e^{-i phi_3 k3} is formed once per x-point and chunk (one entry per thread) and used by
-// A and, conjugated, by E; the k2 factor rides on the twiddles of B and D (and D's
-// carry the nucleus weight).
+// The modulations are products of per-axis factors: a thread forms e^{-i phi_1 j} w^{r j}
+// e^{-i phi_3 k3} for its own j = k2 and broadcasts it along its line's row of lanes, for A
+// and, conjugated, for E; the k2 factor rides on the twiddles of B and D.
 //
-// Bound: FP64 VALU (about 1.2e6 lane instructions per x-point at N_k = 16, 44 % of them
-// the Toeplitz products: 7 ms on 61^3 x-points at full rate) against 1.6 MB of LDS
-// traffic per x-point.  The planes of a chunk take 70 KB at N_k = 16, so two blocks (two
-// waves per SIMD, 196 VGPRs each) share a CU and one's barriers and LDS waits hide
-// behind the other.  Measured on 61^3 x 16^3, FP32 field: 14.7 ms, against 22.1 ms for a
-// form with the chunk's k2-transformed planes side by side in LDS (140 KB, one wave per
-// SIMD, a barrier after every stage).
+// Bound: FP64 VALU (1.35e6 lane instructions per x-point at N_k = 16, 39 % of them the
+// Toeplitz products; 72 % VALU busy) beside 1.1 MB of LDS traffic per x-point.  The planes
+// of a chunk take 35 KB at N_k = 16; three blocks (three waves per SIMD, 168 VGPRs) share a
+// CU, and one's barriers and LDS waits hide behind the others.  The loads whose latency
+// showed (the row of a plane, its kernel values, the line of the next chunk) are issued
+// together ahead of their use.  Measured on 61^3 x 16^3, FP32 field: 13.9 ms; 14.7 ms with
+// two chunks of 16 planes, LDS factor tables and two waves per SIMD; 22.1 ms for a form
+// with the k2-transformed planes side by side in LDS (140 KB, one wave per SIMD, a barrier
+// after every stage).
 template <typename T, int NK>
-__global__ __launch_bounds__(NK * NK, 2) void k_theta(T* __restrict__ fx, const double* __restrict__ kt,
-                                                     const fft::cd* __restrict__ et, const ThetaArgs a,
-                                                     long long total)
+__global__ __launch_bounds__(NK * NK, NK == 16 ? 3 : 4) void k_theta(T* __restrict__ fx, const double* __restrict__ kt,
+                                                                    const fft::cd* __restrict__ et, const ThetaArgs a,
+                                                                    long long total)
 {
     using namespace fft;
     using S = PlaneShape<NK>;
-    constexpr int NT = NK * NK, P = S::P, RS = S::RS;
+    constexpr int NT = NK * NK, P = S::P, RS = S::RS, C = 8, R = P / C;
     constexpr int GROUPS = NT / S::LANES;            // planes worked on at a time
-    __shared__ cd W[NK * S::SLOT];
-    __shared__ cd E02[2][NK * NK];                   // [r][k3][j]
-    __shared__ cd TWF[2][NK], TWD[2][NK];            // [h][k2]
+    static_assert(C % GROUPS == 0, "whole rounds");
+    constexpr bool TAB = NK == 8;                    // factors through LDS (see LineFactors)
+    __shared__ cd W[C * S::SLOT];
+    __shared__ cd TW[TAB ? 2 * 9 : 1], E02[TAB ? NK * 9 : 1];
 
     const int tid = threadIdx.x;
     const int c2 = tid % NK, c3 = tid / NK;          // k1 line (k2, k3) of stages A and E
     const int k3 = tid % NK, h = (tid / NK) & 1, grp = tid / S::LANES;
+    const cd wj = et[c2];                            // w^j, j = c2
 
     for (long long xp = blockIdx.x; xp < total; xp += gridDim.x) {
         T* line = fx + xp * (long long)(NK * NK * NK) + tid * NK;
         double th[NK];
         sfor<0, NK>([&](auto jc) { th[decltype(jc)::value] = 0.0; });
+        T fv[NK];
+        load_raw<T, NK>(line, fv);
 
         for (int nu = 0; nu < a.nnuc; ++nu) {
             const ModRows e = mod_rows_at<NK>(et, a, xp, nu);
-            __syncthreads();   // the previous pass no longer reads the factors
-            {
-                const cd b = cmul(e.e1[c2], e.e3[c3]);   // j = c2 here
-                E02[0][tid] = b;
-                E02[1][tid] = cmul(b, et[c2]);
-            }
-            if (tid < 2 * NK) {
-                const int hh = tid / NK, j = tid % NK;
-                const cd f = hh ? cmul(e.e2[j], et[j]) : e.e2[j];
-                TWF[hh][j] = f;
-                TWD[hh][j] = cd{a.wgt[nu] * f.re, -a.wgt[nu] * f.im};
-            }
-            __syncthreads();
+            const double w = a.wgt[nu];
+            if constexpr (TAB) __syncthreads();      // the previous pass no longer reads the tables
+            LineFactors<NK> tw = half_factors<NK>(et, e.e2, h, tid, TW);
+            cd m02 = cmul(e.e1[c2], e.e3[c3]);       // entry j = c2 of this line's factors
 #pragma unroll 1
-            for (int r = 0; r < 2; ++r) {
+            for (int r = 0; r < R; ++r) {
+                LineFactors<NK> lf;
+                if constexpr (TAB) {
+                    E02[c3 * 9 + c2] = m02;
+                    lf.v = E02 + c3 * 9;
+                    __syncthreads();
+                } else {
+                    lf.v[0] = m02;
+                }
                 {   // A
-                    double fv[NK];
-                    load_k1<T, NK>(line, fv);
-                    cd y[NK];
+                    cd y[C];
                     sfor<0, NK>([&](auto jc) {
                         constexpr int j = decltype(jc)::value;
-                        const cd m = E02[r][c3 * NK + j];
-                        y[j] = cd{m.re * fv[j], m.im * fv[j]};
+                        const cd m = lf.template at<j>();
+                        const double f = (double)fv[j];
+                        if constexpr (j < C) y[j] = cd{m.re * f, m.im * f};
+                        else y[j % C] = cd{fma(m.re, f, y[j % C].re), fma(m.im, f, y[j % C].im)};
                     });
-                    transform<NK, -1>(y);
-                    sfor<0, NK>([&](auto mc) {
+                    transform<C, -1>(y);
+                    sfor<0, C>([&](auto mc) {
                         constexpr int m = decltype(mc)::value;
                         W[m * S::SLOT + c3 * RS + c2] = y[m];
                     });
                 }
                 __syncthreads();
 #pragma unroll 1
-                for (int m = grp; m < NK; m += GROUPS)   // B, C, D: xi1 = r + 2 m, xi2 = 2 k3 + h
-                    plane_conv<NK>(W + m * S::SLOT, kt + ((long long)(r + 2 * m) * P + 2 * k3 + h) * NK, TWF[h],
-                                   TWD[h], k3, h);
+                for (int m = grp; m < C; m += GROUPS)   // B, C, D: xi1 = r + R m, xi2 = 2 k3 + h
+                    plane_conv<NK>(W + m * S::SLOT, kt + ((long long)(r + R * m) * P + 2 * k3 + h) * NK, tw, k3, h);
                 __syncthreads();
+                // the weight rides on E's factors; m02 moves on to the next chunk
+                if constexpr (!TAB) lf.v[0] = cd{w * m02.re, w * m02.im};
+                lf.renew();
+                m02 = cmul(m02, wj);
                 {   // E
-                    cd y[NK];
-                    sfor<0, NK>([&](auto mc) {
+                    load_raw<T, NK>(line, fv);       // for the next chunk's A, ahead of its first use
+                    __builtin_amdgcn_sched_barrier(0);
+                    cd y[C];
+                    sfor<0, C>([&](auto mc) {
                         constexpr int m = decltype(mc)::value;
                         y[m] = W[m * S::SLOT + c3 * RS + c2];
                     });
-                    transform<NK, +1>(y);
+                    transform<C, +1>(y);
+                    if constexpr (TAB) sfor<0, C>([&](auto mc) {
+                        y[decltype(mc)::value].re *= w;
+                        y[decltype(mc)::value].im *= w;
+                    });
                     sfor<0, NK>([&](auto jc) {
                         constexpr int j = decltype(jc)::value;
-                        const cd m = E02[r][c3 * NK + j];
-                        th[j] = fma(m.re, y[j].im, fma(-m.im, y[j].re, th[j]));   // Im(conj(m) y)
+                        const cd m = lf.template at<j>();
+                        th[j] = fma(m.re, y[j % C].im, fma(-m.im, y[j % C].re, th[j]));   // Im(conj(m) y)
                     });
                 }
+                if constexpr (TAB) __syncthreads();  // E02 is rewritten
             }
         }
         store_k1<T, NK>(line, th);

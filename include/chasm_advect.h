@@ -84,8 +84,11 @@ typedef enum {
 typedef enum {
     CHASM_SCHED_AUTO = 0,     /* CUBE when the x-cube fits in LDS, else SLAB; PLAIN on the
                                  runtime-shape kernels */
-    CHASM_SCHED_CUBE = 1,     /* one launch per step, all three sweeps in LDS */
-    CHASM_SCHED_SLAB = 2,     /* two launches per step: x1+x2 on x3-slabs, then x3 */
+    CHASM_SCHED_CUBE = 1,     /* all three sweeps in LDS, up to 64 steps per launch (one per
+                                 launch with per-step diagnostics) */
+    CHASM_SCHED_SLAB = 2,     /* x1 and x2 on x3-slabs, then x3: two launches for up to 64
+                                 steps, which are swept axis by axis; a launch per step and
+                                 one more with per-step diagnostics or observables */
     CHASM_SCHED_PLAIN = 3     /* three launches per step, one per axis */
 } chasm_schedule;
 
@@ -96,8 +99,9 @@ enum {
     /* Allocate a second field of the same shape and dtype (the stage field, one more
      * field of device memory, owned by the handle) and run the sweeps out of place:
      * SLAB and PLAIN read f in their first launch and write the stage field, and write
-     * f back in their last launch, so every step ends in f; CUBE runs the steps of one
-     * chasm_advect_step call in pairs (f -> stage -> f) and an odd last step in place.
+     * f back in their last launch, so every step ends in f; CUBE handles that record
+     * per-step diagnostics run the steps of one chasm_advect_step call in pairs (f ->
+     * stage -> f) and an odd last step in place, others in place.
      * The arithmetic is unchanged (results are bitwise equal to in place); HBM serves a
      * read stream and a write stream to different addresses faster than read-modify-
      * write traffic on one buffer.  chasm_advect_step_many steps CUBE handles in place. */

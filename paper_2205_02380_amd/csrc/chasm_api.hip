@@ -235,6 +235,16 @@ struct chasm_advect_s {
     RtJob rtj[3] = {};
 };
 
+static bool records_steps(const chasm_advect_s* h) { return (h->desc.flags & CHASM_FLAG_REDUCE_EACH_STEP) != 0; }
+
+// Whether a call may sweep several steps axis by axis (SLAB handles): not when every
+// step's field has to exist, and not when FP64 observables are formed, whose values would
+// show the other rounding of an FP32 field.
+static bool axis_by_axis(const chasm_advect_s* h)
+{
+    return (h->desc.flags & (CHASM_FLAG_REDUCE_EACH_STEP | CHASM_FLAG_OBSERVE)) == 0;
+}
+
 static thread_local std::string g_err;
 
 namespace chasm {
@@ -457,9 +467,17 @@ static hipError_t launch_step(const KernelSet* ks, int sched, const Work* const 
 }
 
 // ---------------------------------------------------------------------------
-// SLAB schedule.  A call of K steps alternates the sweep order between steps (x1 x2 x3,
-// then x3 x2 x1, ...; the axis operators commute, see SlabMode), so it runs K + 1
-// passes: pass r is
+// Steps per launch of the multi-step passes: a launch reads and writes the field once
+// whatever its number of steps, so past a few dozen nothing is gained, and the bound
+// keeps single launches short (about 0.2 s for 64 steps of a 34 GB field).
+constexpr int kMultiSteps = 64;
+
+// SLAB schedule.  The axis operators commute (see SlabMode), so a call of K steps whose
+// fields in between nothing asks for (axis_by_axis) runs its sweeps axis by axis, two
+// passes per (at most kMultiSteps) steps:
+//   slab  x1^c x2^c (c = 1: x1 x2),  pencil  x3^c.
+// Otherwise every step's field exists in turn: the sweep order alternates
+// between steps (x1 x2 x3, then x3 x2 x1, ...) and the call runs K + 1 passes: pass r is
 //   r = 0                      slab  x1 x2
 //   r odd,  r < K              pencil x3 x3   (ends step r)
 //   r even, 0 < r < K          slab  x2 x1 | x1 x2   (ends step r)
@@ -467,16 +485,19 @@ static hipError_t launch_step(const KernelSet* ks, int sched, const Work* const 
 //   r = K even                 slab  x2 x1    (ends step K)
 // Every pass but the first ends exactly one step, and a call always ends with the
 // field after its last step.
-enum PassKind { PASS_SLAB_A = 0, PASS_SLAB_B, PASS_SLAB_C, PASS_PENCIL_1, PASS_PENCIL_2 };
+enum PassKind { PASS_SLAB_A = 0, PASS_SLAB_B, PASS_SLAB_C, PASS_SLAB_M, PASS_PENCIL_1, PASS_PENCIL_2, PASS_PENCIL_M };
 
-static int slab_pass_kind(int r, int K)
+// Pass r of an axis_by_axis call of K steps and its steps c; false past the end.
+static bool slab_multi_pass(int r, int K, int* kind, int* c)
 {
-    if (r == 0) return PASS_SLAB_A;
-    if (r % 2) return r == K ? PASS_PENCIL_1 : PASS_PENCIL_2;
-    return r == K ? PASS_SLAB_C : PASS_SLAB_B;
+    const int left = K - (r / 2) * kMultiSteps;
+    if (left <= 0) return false;
+    *c = std::min(left, kMultiSteps);
+    *kind = r % 2 == 0 ? (*c == 1 ? PASS_SLAB_A : PASS_SLAB_M) : (*c == 1 ? PASS_PENCIL_1 : PASS_PENCIL_M);
+    return true;
 }
 
-static bool pass_is_slab(int kind) { return kind <= PASS_SLAB_C; }
+static bool pass_is_slab(int kind) { return kind <= PASS_SLAB_M; }
 
 static hipError_t launch_pass(const KernelSet* ks, int kind, const Work& w, double* part, hipStream_t s)
 {
@@ -484,6 +505,8 @@ static hipError_t launch_pass(const KernelSet* ks, int kind, const Work& w, doub
     case PASS_SLAB_A: return ks->slab[SLAB_X1X2](w, nullptr, s);
     case PASS_SLAB_B: return ks->slab[SLAB_X2X1X1X2](w, part, s);
     case PASS_SLAB_C: return ks->slab[SLAB_X2X1](w, part, s);
+    case PASS_SLAB_M: return ks->slab[SLAB_MULTI](w, nullptr, s);
+    case PASS_PENCIL_M: return ks->pencil_x3n(w, nullptr, s);
     case PASS_PENCIL_1: return ks->pencil_x3(w, part, s);
     default: return ks->pencil_x3x3(w, part, s);
     }
@@ -534,8 +557,6 @@ static hipError_t launch_finalize(chasm_advect_s* h, long long rows, bool record
 // rev: a CUBE step visits the items last to first.  chasm_advect_step alternates the
 // order from step to step, so the items a step stores last are the first ones the next
 // step loads, while they may still sit in the memory-side cache.
-static hipError_t issue_passes(chasm_advect_t h, hipStream_t s, const int* kinds, int n);
-
 static hipError_t issue_step(chasm_advect_t h, hipStream_t s, bool rev = false)
 {
     if (h->rt) {
@@ -545,10 +566,6 @@ static hipError_t issue_step(chasm_advect_t h, hipStream_t s, bool rev = false)
             e = rt_sweep(h->rtj[a], a, h->desc.dtype, (red && a == 2) ? h->partials : nullptr, s);
         if (e == hipSuccess && red) e = launch_finalize(h, h->partial_rows, true, s);
         return e;
-    }
-    if (h->schedule == CHASM_SCHED_SLAB) {
-        const int one[2] = {PASS_SLAB_A, PASS_PENCIL_1};
-        return issue_passes(h, s, one, 2);
     }
     const bool red = (h->desc.flags & CHASM_FLAG_REDUCE_EACH_STEP) != 0;
     double* part = red ? h->partials : nullptr;
@@ -569,7 +586,7 @@ static hipError_t issue_step(chasm_advect_t h, hipStream_t s, bool rev = false)
 // by its reduction when the handle records per-step diagnostics.
 static hipError_t issue_passes(chasm_advect_t h, hipStream_t s, const int* kinds, int n)
 {
-    const bool red = (h->desc.flags & CHASM_FLAG_REDUCE_EACH_STEP) != 0;
+    const bool red = records_steps(h);
     const long long nkp = (long long)h->desc.nk[0] * h->desc.nk[1] * h->desc.nk[2];
     hipError_t e = hipSuccess;
     for (int i = 0; i < n && e == hipSuccess; ++i) {
@@ -601,11 +618,21 @@ static int slab_graph_passes(int g, int* kinds)
     }
 }
 
-// K steps of a SLAB handle: K + 1 passes (slab_pass_kind), as graph replays when the
-// handle has them.
+// K steps of a SLAB handle: the passes of slab_multi_pass, or else K + 1 passes (as graph
+// replays when the handle has them).
 static hipError_t slab_steps(chasm_advect_t h, hipStream_t s, int K)
 {
     if (K <= 0) return hipSuccess;
+    if (axis_by_axis(h)) {
+        hipError_t e = hipSuccess;
+        int kind, c;
+        for (int r = 0; e == hipSuccess && slab_multi_pass(r, K, &kind, &c); ++r) {
+            Work w = *slab_pass_work(h, kind);
+            w.nsteps = c;
+            e = launch_pass(h->ks, kind, w, nullptr, s);
+        }
+        return e;
+    }
     auto run = [&](int g) {
         if (h->sgexec[g]) return hipGraphLaunch(h->sgexec[g], s);
         int kinds[8];
@@ -825,7 +852,10 @@ chasm_status chasm_advect_create(const chasm_advect_desc* desc, void* f_dev, voi
         }
     }
 
-    if (desc->flags & CHASM_FLAG_GRAPH) {
+    // calls that run their steps in a launch or two have nothing to replay
+    const bool few = h->schedule == CHASM_SCHED_CUBE ? !records_steps(h)
+                                                     : h->schedule == CHASM_SCHED_SLAB && axis_by_axis(h);
+    if ((desc->flags & CHASM_FLAG_GRAPH) && !few) {
         if (hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
             return bail(CHASM_EDEVICE, "capture stream creation failed");
         // Capture `steps` steps (pairs when the CUBE steps run out of place) as one graph.
@@ -896,6 +926,17 @@ static chasm_status steps_unobserved(chasm_advect_t h, int32_t nsteps)
         return CHASM_OK;
     }
     const bool cube = h->schedule == CHASM_SCHED_CUBE;
+    if (cube && !records_steps(h)) {   // steps on the resident cube, in place
+        Work w = h->work;
+        for (int32_t s = 0; s < nsteps; s += w.nsteps) {
+            w.nsteps = std::min(nsteps - s, (int32_t)kMultiSteps);
+            w.jobs[0].reverse = h->rev_next;
+            hipError_t e = h->ks->cube(w, nullptr, h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "step launch");
+            h->rev_next = !h->rev_next;
+        }
+        return CHASM_OK;
+    }
     // One step in the current visiting order; the order alternates for CUBE.
     auto single = [&]() {
         const bool rev = cube && h->rev_next;
@@ -949,45 +990,43 @@ chasm_status chasm_advect_step_many(const chasm_advect_t* hs, int32_t n, const i
             const chasm_status st = chasm_advect_step(hs[i], nsteps[i]);
             if (st != CHASM_OK) return st;
         }
-    // The others advance round by round: round r is step r of a CUBE or PLAIN handle and
-    // pass r of a SLAB handle's K + 1 passes (slab_pass_kind), so every job progresses
-    // together.  Handles with the same kernels, schedule and pass share one launch (work
-    // lists of at most kMaxJobs jobs).
+    // The others advance round by round, each by its next launch: some steps of a CUBE
+    // handle, a step of a PLAIN handle, a pass of a SLAB handle (slab_multi_pass), so every
+    // job progresses together.  Handles with the same kernels, schedule and launch share
+    // it (work lists of at most kMaxJobs jobs); CUBE handles share as many steps as all of
+    // them have left, which changes no result.
+    std::vector<int32_t> at(n, 0);   // steps done (CUBE, PLAIN) or passes done (SLAB)
     constexpr int kStep = -1;
-    auto kind_at = [&](int32_t i, int32_t r) -> int {   // what round r runs for handle i (-2: nothing)
-        const int32_t K = nsteps[i];
-        if (hs[i]->schedule == CHASM_SCHED_SLAB) return (K > 0 && r <= K) ? slab_pass_kind(r, K) : -2;
-        return r < K ? kStep : -2;
+    auto next_of = [&](int32_t i, int* kind, int* c) {
+        if (alone(hs[i])) return false;
+        if (hs[i]->schedule == CHASM_SCHED_SLAB) return slab_multi_pass(at[i], nsteps[i], kind, c);
+        *kind = kStep;
+        *c = hs[i]->schedule == CHASM_SCHED_CUBE ? std::min(nsteps[i] - at[i], (int32_t)kMultiSteps) : 1;
+        return at[i] < nsteps[i];
     };
-    int32_t rounds = 0;
-    for (int32_t i = 0; i < n; ++i)
-        if (!alone(hs[i]))
-            rounds = std::max(rounds, hs[i]->schedule == CHASM_SCHED_SLAB && nsteps[i] > 0 ? nsteps[i] + 1 : nsteps[i]);
-    std::vector<int32_t> live;
-    std::vector<int> kinds;
-    for (int32_t r = 0; r < rounds; ++r) {
-        live.clear();
-        kinds.clear();
-        for (int32_t i = 0; i < n; ++i) {
-            if (alone(hs[i])) continue;
-            const int k = kind_at(i, r);
-            if (k == -2) continue;
-            live.push_back(i);
-            kinds.push_back(k);
-        }
-        std::vector<bool> done(live.size(), false);
-        for (size_t a = 0; a < live.size(); ++a) {
-            if (done[a]) continue;
-            chasm_advect_t h = hs[live[a]];
-            const int kind = kinds[a];
+    std::vector<int32_t> group;
+    for (bool more = true; more;) {
+        more = false;
+        std::vector<bool> done(n, false);
+        for (int32_t a = 0; a < n; ++a) {
+            int kind, c;
+            if (done[a] || !next_of(a, &kind, &c)) continue;
+            more = true;
+            chasm_advect_t h = hs[a];
+            const bool cube = h->schedule == CHASM_SCHED_CUBE;
             // One work list per launch; job j of list p is launch p of its handle's step
             // (in place, or through that handle's stage field).
             Work w[3] = {};
-            for (size_t b = a; b < live.size() && w[0].njobs < kMaxJobs; ++b) {
-                chasm_advect_t o = hs[live[b]];
-                if (done[b] || o->ks != h->ks || o->schedule != h->schedule || kinds[b] != kind) continue;
+            group.clear();
+            for (int32_t b = a; b < n && w[0].njobs < kMaxJobs; ++b) {
+                chasm_advect_t o = hs[b];
+                int kb, cb;
+                if (done[b] || o->ks != h->ks || o->schedule != h->schedule || !next_of(b, &kb, &cb) || kb != kind ||
+                    (!cube && cb != c))
+                    continue;
                 const long long items = o->work.jobs[0].nitems;
-                if (w[0].first[w[0].njobs] + items > (1LL << 24)) break;   // keep launch grids small
+                // keep launch grids small; a job above the bound goes alone
+                if (w[0].njobs > 0 && w[0].first[w[0].njobs] + items > (1LL << 24)) break;
                 const Work* pw[3];
                 if (kind == kStep) {
                     step_passes(o, pw);
@@ -999,23 +1038,16 @@ chasm_status chasm_advect_step_many(const chasm_advect_t* hs, int32_t n, const i
                     w[p].first[w[p].njobs + 1] = w[p].first[w[p].njobs] + items;
                     ++w[p].njobs;
                 }
+                c = std::min(c, cb);
                 done[b] = true;
+                group.push_back(b);
             }
-            hipError_t e = hipSuccess;
-            if (w[0].njobs == 0) {   // a single job larger than the per-launch bound
-                if (kind == kStep) {
-                    e = issue_step(h, s);
-                } else {
-                    e = launch_pass(h->ks, kind, *slab_pass_work(h, kind), nullptr, s);
-                }
-                done[a] = true;
-            } else if (kind == kStep) {
-                const Work* pw[3] = {&w[0], &w[1], &w[2]};
-                e = launch_step(h->ks, h->schedule, pw, nullptr, s);
-            } else {
-                e = launch_pass(h->ks, kind, w[0], nullptr, s);
-            }
+            w[0].nsteps = c;
+            const Work* pw[3] = {&w[0], &w[1], &w[2]};
+            const hipError_t e = kind == kStep ? launch_step(h->ks, h->schedule, pw, nullptr, s)
+                                               : launch_pass(h->ks, kind, w[0], nullptr, s);
             if (e != hipSuccess) return hip_fail(h, e, "batched step launch");
+            for (int32_t b : group) at[b] += cube ? c : 1;
         }
     }
     return CHASM_OK;

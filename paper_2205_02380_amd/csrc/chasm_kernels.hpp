@@ -49,6 +49,7 @@ struct JobDev {
 constexpr int kMaxJobs = 24;
 struct Work {
     int njobs;
+    int nsteps;            // steps per launch of the multi-step passes (0 or 1: one)
     long long first[kMaxJobs + 1];
     JobDev jobs[kMaxJobs];
 };
@@ -255,8 +256,15 @@ __device__ __forceinline__ void write_partials(double (&acc)[5], const int ik[3]
 // round -- or, after the last round, the next item's first round -- is already in
 // flight into VGPRs (N/VW 16-byte buffer loads per lane).  The x3 sweep then runs on
 // the whole cube and the result streams out, with the FP64 partials when asked for.
-template <typename T, int N, int M, int G, int CL, int NT, bool RED>
-__global__ __launch_bounds__(NT) void k_cube(const Work w, double* __restrict__ partials)
+// MULTI: a launch runs w.nsteps steps on the resident cube (x1 x2 x3 per step, the
+// arithmetic and order of one launch per step, bitwise): the field is read and written
+// once per launch instead of once per step, so the launch is bound by the line
+// arithmetic, not by HBM: 32^3 x 16^3 FP32, 20 steps in a call, 1.90 ms against 3.62 ms;
+// 16^3 x 8^3 FP64, 10 steps, 38 us against 157 us (ten launches).  It is a kernel of its own
+// because the step loop costs registers: one kernel for both took a one-step launch of
+// six 24^3 x 12^3 jobs from 264 to 422 us (one resident block per CU instead of two).
+template <typename T, int N, int M, int G, int CL, int NT, bool RED, bool MULTI = false, int WPE = 1>
+__global__ __launch_bounds__(NT, WPE) void k_cube(const Work w, double* __restrict__ partials)
 {
     constexpr int PX = N + 1;
     constexpr int VW = Vec16<T>::n;
@@ -330,49 +338,57 @@ __global__ __launch_bounds__(NT) void k_cube(const Work w, double* __restrict__ 
         const auto k0 = axis_coef<T>(job, 0, ik[0], sig0);
         const auto k1 = axis_coef<T>(job, 1, ik[1], sig1);
 
+        static_assert(!(RED && MULTI), "partials describe one step");
+        const int nsteps = MULTI ? w.nsteps : 1;
 #pragma unroll 1
-        for (int r = 0; r < ROUNDS; ++r) {
-            if (r > 0) fill(r);
-            __syncthreads();
-            if (r + 1 < ROUNDS) fetch(item, r + 1);
-            else if (next < total) fetch(next, 0);
-            const unsigned plane = r * PL + plane_t;
-            {   // x1: row (x2 = lane_t) of this thread's plane
-                T* row = lds + (plane * N + lane_t) * PX;
-                dispatch_sigma(sig0, [&](auto sc) {
-                    T v[N];
+        for (int st = 0; st < nsteps; ++st) {
+#pragma unroll 1
+            for (int r = 0; r < ROUNDS; ++r) {
+                if (st == 0 && r > 0) fill(r);
+                __syncthreads();
+                if (r + 1 < ROUNDS) {
+                    if (st == 0) fetch(item, r + 1);
+                } else if (st + 1 == nsteps && next < total) {
+                    fetch(next, 0);
+                }
+                const unsigned plane = r * PL + plane_t;
+                {   // x1: row (x2 = lane_t) of this thread's plane
+                    T* row = lds + (plane * N + lane_t) * PX;
+                    dispatch_sigma(sig0, [&](auto sc) {
+                        T v[N];
 #pragma unroll
-                    for (int i = 0; i < N; ++i) v[i] = row[i];
-                    advect_line<T, N, M, G, CL, decltype(sc)::value>(v, k0, sig0, [&](int j, T x) { row[j] = x; });
-                });
+                        for (int i = 0; i < N; ++i) v[i] = row[i];
+                        advect_line<T, N, M, G, CL, decltype(sc)::value>(v, k0, sig0, [&](int j, T x) { row[j] = x; });
+                    });
+                }
+                __syncthreads();
+                {   // x2: column (x1 = lane_t) of this thread's plane
+                    T* col = lds + plane * N * PX + lane_t;
+                    dispatch_sigma(sig1, [&](auto sc) {
+                        T v[N];
+#pragma unroll
+                        for (int i = 0; i < N; ++i) v[i] = col[i * PX];
+                        advect_line<T, N, M, G, CL, decltype(sc)::value>(v, k1, sig1,
+                                                                           [&](int j, T x) { col[j * PX] = x; });
+                    });
+                }
             }
             __syncthreads();
-            {   // x2: column (x1 = lane_t) of this thread's plane
-                T* col = lds + plane * N * PX + lane_t;
-                dispatch_sigma(sig1, [&](auto sc) {
-                    T v[N];
+            {   // x3 over the whole cube: lines (x1, x2) = (l % N, l / N), l = tid + q*NT
+                int sig2;
+                const auto k2 = axis_coef<T>(job, 2, ik[2], sig2);
+                const unsigned lbase = plane_t * PX + lane_t;
+                dispatch_sigma(sig2, [&](auto sc) {
+                    constexpr int SIG = decltype(sc)::value;
+                    static_for<0, N * N / NT>([&](auto qc) {
+                        T* line = lds + lbase + (unsigned)(decltype(qc)::value * PL * PX);
+                        T v[N];
 #pragma unroll
-                    for (int i = 0; i < N; ++i) v[i] = col[i * PX];
-                    advect_line<T, N, M, G, CL, decltype(sc)::value>(v, k1, sig1,
-                                                                       [&](int j, T x) { col[j * PX] = x; });
+                        for (int i = 0; i < N; ++i) v[i] = line[i * N * PX];
+                        advect_line<T, N, M, G, CL, SIG>(v, k2, sig2, [&](int j, T x) { line[j * N * PX] = x; });
+                    });
                 });
             }
-        }
-        __syncthreads();
-        {   // x3 over the whole cube: lines (x1, x2) = (l % N, l / N), l = tid + q*NT
-            int sig2;
-            const auto k2 = axis_coef<T>(job, 2, ik[2], sig2);
-            const unsigned lbase = plane_t * PX + lane_t;
-            dispatch_sigma(sig2, [&](auto sc) {
-                constexpr int SIG = decltype(sc)::value;
-                static_for<0, N * N / NT>([&](auto qc) {
-                    T* line = lds + lbase + (unsigned)(decltype(qc)::value * PL * PX);
-                    T v[N];
-#pragma unroll
-                    for (int i = 0; i < N; ++i) v[i] = line[i * N * PX];
-                    advect_line<T, N, M, G, CL, SIG>(v, k2, sig2, [&](int j, T x) { line[j * N * PX] = x; });
-                });
-            });
         }
         __syncthreads();
 
@@ -428,12 +444,64 @@ __global__ __launch_bounds__(NT) void k_cube(const Work w, double* __restrict__ 
 //   SLAB_X1X2      x1 x2              (first pass of a step)
 //   SLAB_X2X1X1X2  x2 x1 | x1 x2      (the end of one step and the start of the next)
 //   SLAB_X2X1      x2 x1              (the end of the last step of a call)
+//   SLAB_MULTI     x1 (w.nsteps times) x2 (w.nsteps times)
 // Consecutive steps of a multi-step call alternate the sweep order, x1 x2 x3 then
 // x3 x2 x1: the three axis operators act on different indices of the tensor-product
 // spline (eqs. 3.11-3.12) and commute exactly, so the order changes only the rounding.
 // Adjacent sweeps along the same axes then share a pass: K steps take K + 1 passes
-// (slab, pencil, slab, ...), one read and one write of the field per pass.
-enum SlabMode { SLAB_X1 = 0, SLAB_X1X2 = 1, SLAB_X2X1X1X2 = 2, SLAB_X2X1 = 3 };
+// (slab, pencil, slab, ...), one read and one write of the field per pass.  When no
+// diagnostics of the steps in between are asked for, all sweeps of a call along one axis
+// are adjacent: K steps take two passes, SLAB_MULTI and the multi-sweep pencil, in which
+// a line stays in registers from sweep to sweep; they are bound by the line arithmetic
+// (64^3 x 16^3 FP32, 8 steps in a call: 5.26 ms against 13.56 ms in nine passes; 48^3 x 12^3
+// FP64, 4 steps: 1.51 against 2.90 ms).
+enum SlabMode { SLAB_X1 = 0, SLAB_X1X2 = 1, SLAB_X2X1X1X2 = 2, SLAB_X2X1 = 3, SLAB_MULTI = 4 };
+
+// n sweeps of one line held in registers, v -> v, two at a time so that the line changes
+// registers without moves.  The cells of a shift class without a straight-line store go
+// through the compile-time barrel shifter (pencils, which have no LDS row), so no register
+// array is indexed at run time.
+template <typename T, int N, int M, int G, int CL, int SIG>
+__device__ __forceinline__ void sweep_line(T (&v)[N], const AxisCoef<T>& k, int sigma, int n)
+{
+    auto sweep = [&](const T (&from)[N], T (&to)[N]) {
+        if constexpr (SIG != SIG_ANY) {
+            advect_line<T, N, M, G, CL, SIG>(from, k, sigma, [&](int j, T x) { to[j] = x; });
+        } else {
+            T cv[N + 7];
+            line_cells<T, N, M, G, CL>(from, cv, k);
+            store_cells<T, N, SIG_ANY>(cv, sigma, [&](int j, T x) { to[j] = x; });
+        }
+    };
+    T y[N];
+    if constexpr (SIG != SIG_ANY) {
+#pragma unroll 1
+        for (; n > 1; n -= 2) {
+            sweep(v, y);
+            sweep(y, v);
+        }
+    }
+#pragma unroll 1
+    for (; n > 0; --n) {
+        sweep(v, y);
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = y[i];
+    }
+}
+
+// n sweeps of one line in LDS (node i at p[i * STRIDE]) that no other thread touches: for
+// lines that would not leave room for two copies in registers.
+template <typename T, int N, int M, int G, int CL, int SIG, int STRIDE>
+__device__ __forceinline__ void sweep_lds(T* p, const AxisCoef<T>& k, int sigma, int n)
+{
+#pragma unroll 1
+    for (int s = 0; s < n; ++s) {
+        T v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = p[i * STRIDE];
+        advect_line<T, N, M, G, CL, SIG>(v, k, sigma, [&](int j, T x) { p[j * STRIDE] = x; });
+    }
+}
 
 // S x3-slabs (N x N each) per block in LDS, block = S*N threads (one line each per
 // sweep).  Persistent over units of S consecutive slabs of one item.  PRE: the next
@@ -455,6 +523,9 @@ __global__ __launch_bounds__(S * N) void k_slab(const Work w, double* __restrict
     using V = typename Vec16<T>::type;
     __shared__ T lds[S * N * PX];
 
+    // multi-sweep lines in registers, or (FP64 lines of 48 and 64 nodes, and shifts of a cell
+    // or more) through LDS
+    constexpr bool LINE_REG = sizeof(T) * N <= 256;
     constexpr int BPI = N / S;                     // units per item
     const long long units = w.first[w.njobs] * BPI;
     long long u = blockIdx.x;
@@ -530,7 +601,20 @@ __global__ __launch_bounds__(S * N) void k_slab(const Work w, double* __restrict
             const auto kc = axis_coef<T>(job, 0, ik[0], sigma);
             T* row = lds + threadIdx.x * PX;
             constexpr bool X1REG = MODE == SLAB_X2X1X1X2 && sizeof(T) == 4 && N <= 64;
-            if constexpr (X1REG) {
+            if constexpr (MODE == SLAB_MULTI) {
+                dispatch_sigma(sigma, [&](auto sc) {
+                    if constexpr (LINE_REG && decltype(sc)::value != SIG_ANY) {
+                        T v[N];
+#pragma unroll
+                        for (int i = 0; i < N; ++i) v[i] = row[i];
+                        sweep_line<T, N, M, G, CL, decltype(sc)::value>(v, kc, sigma, w.nsteps);
+#pragma unroll
+                        for (int i = 0; i < N; ++i) row[i] = v[i];
+                    } else {
+                        sweep_lds<T, N, M, G, CL, decltype(sc)::value, 1>(row, kc, sigma, w.nsteps);
+                    }
+                });
+            } else if constexpr (X1REG) {
                 dispatch_sigma(sigma, [&](auto sc) {
                     constexpr int SIG = decltype(sc)::value;
                     T v[N], y[N];
@@ -589,11 +673,19 @@ __global__ __launch_bounds__(S * N) void k_slab(const Work w, double* __restrict
             const Buf ob(out_ptr, UNIT_BYTES);
             const uint32_t voff = (uint32_t)((slab_t * N * N + col_t) * sizeof(T));
             dispatch_sigma(sigma, [&](auto sc) {
+                constexpr bool IN_REG = LINE_REG && decltype(sc)::value != SIG_ANY;
+                if constexpr (MODE == SLAB_MULTI && !IN_REG)
+                    sweep_lds<T, N, M, G, CL, decltype(sc)::value, PX>(lds + base, kc, sigma, w.nsteps - 1);
                 T v[N];
 #pragma unroll
                 for (int i = 0; i < N; ++i) v[i] = lds[base + i * PX];
-                advect_line<T, N, M, G, CL, decltype(sc)::value>(
-                    v, kc, sigma, [&](int j, T x) { ob.template store<T, CP>(x, voff, (uint32_t)(j * N * sizeof(T))); });
+                auto put = [&](int j, T x) { ob.template store<T, CP>(x, voff, (uint32_t)(j * N * sizeof(T))); };
+                if constexpr (MODE == SLAB_MULTI && IN_REG) {
+                    sweep_line<T, N, M, G, CL, decltype(sc)::value>(v, kc, sigma, w.nsteps);
+                    static_for<0, N>([&](auto jc) { put(decltype(jc)::value, v[decltype(jc)::value]); });
+                } else {
+                    advect_line<T, N, M, G, CL, decltype(sc)::value>(v, kc, sigma, put);
+                }
             });
         }
         if constexpr (RED) {
@@ -610,7 +702,8 @@ __global__ __launch_bounds__(S * N) void k_slab(const Work w, double* __restrict
 // ---------------------------------------------------------------------------
 // One line per lane along axis AXIS (1: x2, 2: x3), NT lines per block; NT divides
 // N*N so a block never straddles two items.  NSW sweeps along the axis (2: the x3
-// sweep that ends one step and the x3 sweep that starts the next, see SlabMode).
+// sweep that ends one step and the x3 sweep that starts the next, see SlabMode;
+// 0: w.nsteps sweeps).
 // RED: FP64 partials of the field after the first sweep, one row per block.
 // OBS (one x3 sweep): partials is the item rows of the observables instead; each lane
 // holds its (x1, x2) column after the sweep, so it forms the column sum q and, with
@@ -620,7 +713,7 @@ template <typename T, int N, int M, int G, int CL, int NT, int AXIS, int NSW, bo
 __global__ __launch_bounds__(NT) void k_pencil(const Work w, double* __restrict__ partials)
 {
     static_assert((N * N) % NT == 0, "block must tile the lines of one item");
-    static_assert(NSW == 1 || NSW == 2, "one or two sweeps");
+    static_assert(NSW >= 0 && NSW <= 2 && !(NSW == 0 && RED), "one, two or w.nsteps sweeps");
     constexpr int BPI = N * N / NT;
     long long item;
     const JobDev& job = job_of(w, blockIdx.x / BPI, item);
@@ -682,7 +775,10 @@ __global__ __launch_bounds__(NT) void k_pencil(const Work w, double* __restrict_
     auto store = [&](int j, T x) { obuf.store<T>(x, voff, j * sstride); };
     dispatch_sigma(sigma, [&](auto sc) {
         constexpr int SIG = decltype(sc)::value;
-        if constexpr (NSW == 1) {
+        if constexpr (NSW == 0) {
+            sweep_line<T, N, M, G, CL, SIG>(v, kc, sigma, w.nsteps);
+            static_for<0, N>([&](auto jc) { store(decltype(jc)::value, v[decltype(jc)::value]); });
+        } else if constexpr (NSW == 1) {
             advect_line<T, N, M, G, CL, SIG>(v, kc, sigma, [&](int j, T x) {
                 store(j, x);
                 tally(j, x);

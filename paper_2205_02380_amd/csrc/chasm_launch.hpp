@@ -24,6 +24,11 @@ struct Launch {
     // FP32 uses one line per thread per sweep up to N = 32 (4 waves per SIMD)
     static constexpr int cube_nt =
         N <= 8 ? 64 : (N <= 16 ? 256 : (N <= 24 ? (sizeof(T) == 4 ? 576 : 192) : 1024));
+    // Waves per SIMD asked of the multi-step cube (register bound): those of the blocks
+    // whose cubes fit in a CU's LDS together, at most 5.
+    static constexpr int cube_blocks = (int)(kLdsBytes / ((size_t)N * N * (N + 1) * sizeof(T) + 512));
+    static constexpr int cube_waves = (cube_blocks * (cube_nt / 64) + 3) / 4;
+    static constexpr int cube_wpe = cube_waves < 1 ? 1 : cube_waves > 5 ? 5 : cube_waves;
     // x3-slabs per slab block: S*N threads, a multiple of 64, S | N.
     static constexpr int slab_s0 = N == 8 ? 8 : (N == 16 ? 4 : (N == 24 ? 8 : (N == 32 ? 2 : (N == 48 ? 4 : 1))));
     static constexpr int slab_s = TILE == 1 ? 2 * slab_s0 : slab_s0;
@@ -78,6 +83,8 @@ hipError_t launch_cube(const Work& w, double* partials, hipStream_t s)
     if constexpr (Lc::cube_fits) {
         constexpr int NT = Lc::cube_nt;
         const long long items = w.first[w.njobs];
+        if (!partials && w.nsteps > 1)
+            return launch_persistent<k_cube<T, N, M, G, CL, NT, false, true, Lc::cube_wpe>>(NT, items, s, w, partials);
         return partials ? launch_persistent<k_cube<T, N, M, G, CL, NT, true>>(NT, items, s, w, partials)
                         : launch_persistent<k_cube<T, N, M, G, CL, NT, false>>(NT, items, s, w, partials);
     } else {
@@ -90,7 +97,7 @@ hipError_t launch_slab(const Work& w, double* partials, hipStream_t s)
 {
     using Lc = Launch<T, N, TILE>;
     constexpr int S = Lc::slab_s;
-    constexpr bool PRE = MODE != SLAB_X2X1X1X2 && Lc::slab_pre;
+    constexpr bool PRE = MODE != SLAB_X2X1X1X2 && MODE != SLAB_MULTI && Lc::slab_pre;
     constexpr int CP = Lc::slab_cpol;
     const long long units = w.first[w.njobs] * (N / S);
     if constexpr (MODE == SLAB_X2X1X1X2 || MODE == SLAB_X2X1) {
@@ -106,9 +113,9 @@ hipError_t launch_pencil(const Work& w, double* partials, hipStream_t s)
     using Lc = Launch<T, N, TILE>;
     constexpr int NT = Lc::pencil_nt;
     const unsigned grid = (unsigned)(w.first[w.njobs] * (N * N / NT));
-    if (AXIS == 2 && partials)
-        hipLaunchKernelGGL((k_pencil<T, N, M, G, CL, NT, AXIS, NSW, AXIS == 2>), dim3(grid), dim3(NT), 0, s, w,
-                           partials);
+    if (AXIS == 2 && NSW != 0 && partials)
+        hipLaunchKernelGGL((k_pencil<T, N, M, G, CL, NT, AXIS, NSW, AXIS == 2 && NSW != 0>), dim3(grid), dim3(NT), 0, s,
+                           w, partials);
     else
         hipLaunchKernelGGL((k_pencil<T, N, M, G, CL, NT, AXIS, NSW, false>), dim3(grid), dim3(NT), 0, s, w, partials);
     return hipGetLastError();
@@ -148,10 +155,12 @@ const KernelSet* kernel_set()
         // the cube schedule has one launch shape (tile 0)
         (TILE == 0 && Lc::cube_fits) ? &launch_cube<T, N, M, G, CL> : nullptr,
         {&launch_slab<T, N, M, G, CL, SLAB_X1, TILE>, &launch_slab<T, N, M, G, CL, SLAB_X1X2, TILE>,
-         &launch_slab<T, N, M, G, CL, SLAB_X2X1X1X2, TILE>, &launch_slab<T, N, M, G, CL, SLAB_X2X1, TILE>},
+         &launch_slab<T, N, M, G, CL, SLAB_X2X1X1X2, TILE>, &launch_slab<T, N, M, G, CL, SLAB_X2X1, TILE>,
+         &launch_slab<T, N, M, G, CL, SLAB_MULTI, 0>},
         &launch_pencil<T, N, M, G, CL, 1, 1, TILE>,
         &launch_pencil<T, N, M, G, CL, 2, 1, TILE>,
         &launch_pencil<T, N, M, G, CL, 2, 2, TILE>,
+        &launch_pencil<T, N, M, G, CL, 2, 0, 0>,
         &launch_pencil_obs<T, N, M, G, CL, TILE>,
         &launch_reduce<T, N>,
         1,
@@ -161,7 +170,14 @@ const KernelSet* kernel_set()
     return &ks;
 }
 
-#define CHASM_INSTANTIATE(T, N, M, G, CL) template const KernelSet* kernel_set<T, N, M, G, CL, 0>();
-#define CHASM_INSTANTIATE_TILE(T, N, M, G, CL, TILE) template const KernelSet* kernel_set<T, N, M, G, CL, TILE>();
+#define CHASM_INSTANTIATE(T, N, M, G, CL)                                                                    \
+    template hipError_t launch_slab<T, N, M, G, CL, SLAB_MULTI, 0>(const Work&, double*, hipStream_t);       \
+    template hipError_t launch_pencil<T, N, M, G, CL, 2, 0, 0>(const Work&, double*, hipStream_t);           \
+    template const KernelSet* kernel_set<T, N, M, G, CL, 0>();
+// the multi-step passes have one launch shape: a tile variant takes tile 0's
+#define CHASM_INSTANTIATE_TILE(T, N, M, G, CL, TILE)                                                         \
+    extern template hipError_t launch_slab<T, N, M, G, CL, SLAB_MULTI, 0>(const Work&, double*, hipStream_t); \
+    extern template hipError_t launch_pencil<T, N, M, G, CL, 2, 0, 0>(const Work&, double*, hipStream_t);    \
+    template const KernelSet* kernel_set<T, N, M, G, CL, TILE>();
 
 }  // namespace chasm

@@ -21,11 +21,13 @@ struct KernelSet {
     int tile;               // launch-shape variant (chasm_launch.hpp)
     LaunchFn cube;          // nullptr when the x-cube does not fit in LDS
     // x3-slab passes by sweep sequence: [0] x1, [1] x1 x2, [2] x2 x1 x1 x2 (partials
-    // after the first x1), [3] x2 x1 (partials after x1)
-    LaunchFn slab[4];
+    // after the first x1), [3] x2 x1 (partials after x1), [4] x1^n x2^n (n = nsteps of the
+    // work list)
+    LaunchFn slab[5];
     LaunchFn pencil_x2;
     LaunchFn pencil_x3;     // partials after the x3 sweep
     LaunchFn pencil_x3x3;   // two x3 sweeps, partials after the first
+    LaunchFn pencil_x3n;    // nsteps x3 sweeps, no partials
     LaunchFn pencil_x3_obs; // one x3 sweep writing the observables' item rows (chasm_obs.hpp)
     LaunchFn reduce;        // diagnostics of the current field (one partial row per item)
     int cube_rows;          // partial rows per item written by cube (1)

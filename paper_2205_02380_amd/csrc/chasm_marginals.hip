@@ -7,10 +7,17 @@
 //                 chasm_obs.hpp (column sums q over x3, plane sums G of 64-column
 //                 groups), read once from HBM; each wave takes one 64-column group at
 //                 a time, so every load of a wave is a contiguous run of x1;
-//   k_marg_sum    one thread per output value, summing the item rows in a fixed order
-//                 and scaling by the cell volume of the integrated variables.
+//   k_marg_axes   per item, the row's contributions to the three W: a[x1] = sum of q over
+//                 x2, b[x2] = sum of q over x1, c[x3] = sum of G over the groups;
+//   k_marg_cols   P: one thread per column (x2, x1) and chunk of items, the sum of q;
+//   k_marg_sum    one wave per W value, summing its items' contributions, and one thread
+//                 per P value, summing the chunks; scales by the cell volume of the
+//                 integrated variables.
+// Every sum runs in a fixed order.  One thread per output value, walking the item rows by
+// itself, took 3.1 ms on 61^3 x 10^3 (59 MB of rows); k_marg_axes 32 us, k_marg_cols 7 and
+// k_marg_sum 18 take its place.
 // The x3 sweep that ends an observed step (CHASM_FLAG_OBSERVE) writes the same rows in
-// its epilogue; k_marg_sum then completes the observables without reading the field.
+// its epilogue; the sums then complete the observables without reading the field.
 #include <hip/hip_runtime.h>
 
 #include <string>
@@ -48,71 +55,120 @@ __global__ __launch_bounds__(256) void k_marg_item(const T* __restrict__ f, int 
 struct MargArgs {
     int nx[3], nk[3], nbatch;
     double s[4];                 // cell volumes of the integrated variables: W1, W2, W3, P
+    int chunks;                  // of the items of a batch member, for P
 };
 
-// out layout per batch member b: W1[k1][x1] | W2[k2][x2] | W3[k3][x3] | P[x2][x1].
-// Per item: W1 takes a[x1] = sum over x2 of q (ascending x2), W2 b[x2] = sum over x1 of
-// q (ascending x1), W3 c[x3] = sum over the groups of G (ascending), P the q itself;
-// the items are summed k3 outermost, then k2, then k1.
-__global__ __launch_bounds__(256) void k_marg_sum(const double* __restrict__ part, MargArgs a,
-                                                  double* __restrict__ out)
+// Doubles of the second stage's workspace: per item a | b | c, then per chunk of a batch
+// member's items the partial P.
+static long long marg_axes(const int nx[3]) { return (long long)nx[0] + nx[1] + nx[2]; }
+
+// Chunks of a batch member's nkp items: enough threads for the chip, at least 16 items each.
+static int marg_chunks(const int nx[3], long long nkp)
 {
-    const int N0 = a.nx[0], N1 = a.nx[1], N2 = a.nx[2], n1 = a.nk[0], n2 = a.nk[1], n3 = a.nk[2];
-    const long long ROW = obs_row(N0, N1, N2);
-    const long long NG = obs_groups(N0, N1);
-    const long long plane = (long long)N0 * N1;
-    const long long per_b = (long long)N0 * n1 + (long long)N1 * n2 + (long long)N2 * n3 + plane;
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= per_b * a.nbatch) return;
-    const int b = (int)(gid / per_b);
-    long long r = gid % per_b;
-    const double* base = part + (long long)b * n1 * n2 * n3 * ROW;
-    auto item = [&](int k1, int k2, int k3) { return base + (((long long)k3 * n2 + k2) * n1 + k1) * ROW; };
-    double s = 0.0, scale;
-    if (r < (long long)N0 * n1) {
-        const int k1 = (int)(r / N0), x = (int)(r % N0);
-        for (int k3 = 0; k3 < n3; ++k3)
-            for (int k2 = 0; k2 < n2; ++k2) {
-                const double* q = item(k1, k2, k3);
-                double t = 0.0;
-                for (int y = 0; y < N1; ++y) t += q[(long long)y * N0 + x];
-                s += t;
-            }
-        scale = a.s[0];
-    } else if ((r -= (long long)N0 * n1) < (long long)N1 * n2) {
-        const int k2 = (int)(r / N1), y = (int)(r % N1);
-        for (int k3 = 0; k3 < n3; ++k3)
-            for (int k1 = 0; k1 < n1; ++k1) {
-                const double* q = item(k1, k2, k3) + (long long)y * N0;
-                double t = 0.0;
-                for (int x = 0; x < N0; ++x) t += q[x];
-                s += t;
-            }
-        scale = a.s[1];
-    } else if ((r -= (long long)N1 * n2) < (long long)N2 * n3) {
-        const int k3 = (int)(r / N2), z = (int)(r % N2);
-        for (int k2 = 0; k2 < n2; ++k2)
-            for (int k1 = 0; k1 < n1; ++k1) {
-                const double* G = item(k1, k2, k3) + plane;
-                double t = 0.0;
-                for (long long g = 0; g < NG; ++g) t += G[g * N2 + z];
-                s += t;
-            }
-        scale = a.s[2];
-    } else {
-        r -= (long long)N2 * n3;                         // (x2, x1) = r
-        for (int k3 = 0; k3 < n3; ++k3)
-            for (int k2 = 0; k2 < n2; ++k2)
-                for (int k1 = 0; k1 < n1; ++k1) s += item(k1, k2, k3)[r];
-        scale = a.s[3];
-    }
-    out[gid] = s * scale;
+    const long long want = (256LL * 2048) / ((long long)nx[0] * nx[1]) + 1;
+    const long long most = (nkp + 15) / 16;
+    return (int)(want < most ? want : most);
 }
 
-// Rows of FP64 item partials the marginals need per item (chasm_obs.hpp).
-long long marginal_row(const int nx[3]) { return obs_row(nx[0], nx[1], nx[2]); }
+__global__ __launch_bounds__(256) void k_marg_axes(const double* __restrict__ part, MargArgs a, double* __restrict__ axes)
+{
+    __shared__ double red[4][64];
+    const int N0 = a.nx[0], N1 = a.nx[1], N2 = a.nx[2];
+    const long long item = blockIdx.x;
+    const double* q = part + item * obs_row(N0, N1, N2);
+    const double* G = q + (long long)N0 * N1;
+    double* out = axes + item * (N0 + N1 + N2);
+    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+    // sums down the columns of a rows x cols matrix, 64 columns at a time: wave w takes the
+    // rows w, w + 4, ...; the four partial sums are added in wave order
+    auto down = [&](const double* m, long long rows, int cols, double* dst) {
+        for (int c0 = 0; c0 < cols; c0 += 64) {
+            const int c = c0 + ln;
+            double t = 0.0;
+            if (c < cols)
+                for (long long r = wv; r < rows; r += 4) t += m[r * cols + c];
+            red[wv][ln] = t;
+            __syncthreads();
+            if (wv == 0 && c < cols) dst[c] = (red[0][ln] + red[1][ln]) + (red[2][ln] + red[3][ln]);
+            __syncthreads();
+        }
+    };
+    down(q, N1, N0, out);
+    down(G, obs_groups(N0, N1), N2, out + N0 + N1);
+    for (int y = wv; y < N1; y += 4) {               // a wave per row
+        double t = 0.0;
+        for (int x = ln; x < N0; x += 64) t += q[(long long)y * N0 + x];
+        t = obs_wave_sum(t);
+        if (ln == 0) out[N0 + y] = t;
+    }
+}
 
-// Both passes on stream st: part holds nitems * marginal_row(nx) doubles, out
+__global__ __launch_bounds__(256) void k_marg_cols(const double* __restrict__ part, MargArgs a, double* __restrict__ cols)
+{
+    const long long plane = (long long)a.nx[0] * a.nx[1], nkp = (long long)a.nk[0] * a.nk[1] * a.nk[2];
+    const unsigned tiles = (unsigned)((plane + 255) / 256), u = blockIdx.x / tiles;
+    const long long c = (long long)(blockIdx.x % tiles) * 256 + threadIdx.x;
+    if (c >= plane) return;
+    const long long ch = u % a.chunks, b = u / a.chunks;
+    const long long per = (nkp + a.chunks - 1) / a.chunks, i0 = ch * per, i1 = i0 + per < nkp ? i0 + per : nkp;
+    const long long row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
+    const double* q = part + b * nkp * row + c;
+    double t = 0.0;
+#pragma unroll 8
+    for (long long i = i0; i < i1; ++i) t += q[i * row];
+    cols[((long long)b * a.chunks + ch) * plane + c] = t;
+}
+
+// out layout per batch member b: W1[k1][x1] | W2[k2][x2] | W3[k3][x3] | P[x2][x1].
+__global__ __launch_bounds__(256) void k_marg_sum(const double* __restrict__ axes, const double* __restrict__ cols,
+                                                  MargArgs a, double* __restrict__ out)
+{
+    const int N0 = a.nx[0], N1 = a.nx[1], N2 = a.nx[2], n1 = a.nk[0], n2 = a.nk[1], n3 = a.nk[2];
+    const long long plane = (long long)N0 * N1, nkp = (long long)n1 * n2 * n3;
+    const long long nw = (long long)N0 * n1 + (long long)N1 * n2 + (long long)N2 * n3, per_b = nw + plane;
+    const long long wblocks = (nw * a.nbatch + 3) / 4;
+    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63, A = N0 + N1 + N2;
+    if (blockIdx.x < wblocks) {                      // a wave per W value
+        const long long id = (long long)blockIdx.x * 4 + wv;
+        if (id >= nw * a.nbatch) return;
+        const int b = (int)(id / nw);
+        long long r = id % nw;
+        const double* base = axes + b * nkp * A;
+        // axis d, its node j and k index kd; the items of kd: i = lo + hi * stride
+        int d = 0;
+        const int N[3] = {N0, N1, N2}, n[3] = {n1, n2, n3};
+        while (d < 2 && r >= (long long)N[d] * n[d]) r -= (long long)N[d] * n[d++];
+        const int kd = (int)(r / N[d]), j = (int)(r % N[d]);
+        const long long inner = d == 0 ? 1 : d == 1 ? n1 : (long long)n1 * n2;   // stride of k_d
+        const long long rest = nkp / n[d];
+        const double* v = base + (d == 0 ? 0 : d == 1 ? N0 : N0 + N1) + j;
+        double t = 0.0;
+        for (long long u = ln; u < rest; u += 64) {
+            const long long i = (u / inner) * inner * n[d] + kd * inner + u % inner;
+            t += v[i * A];
+        }
+        t = obs_wave_sum(t);
+        if (ln == 0) out[b * per_b + id % nw] = t * a.s[d];
+    } else {                                         // a thread per P value
+        const long long id = ((long long)blockIdx.x - wblocks) * 256 + threadIdx.x;
+        if (id >= plane * a.nbatch) return;
+        const long long b = id / plane, c = id % plane;
+        double t = 0.0;
+        for (int ch = 0; ch < a.chunks; ++ch) t += cols[(b * a.chunks + ch) * plane + c];
+        out[b * per_b + nw + c] = t * a.s[3];
+    }
+}
+
+// Doubles of the workspace of a field's marginals: the item rows (chasm_obs.hpp), then the
+// second stage's sums.
+long long marginal_workspace(const int nx[3], const int nk[3], int nbatch)
+{
+    const long long nkp = (long long)nk[0] * nk[1] * nk[2];
+    return nkp * nbatch * (obs_row(nx[0], nx[1], nx[2]) + marg_axes(nx)) +
+           (long long)marg_chunks(nx, nkp) * nbatch * nx[0] * nx[1];
+}
+
+// All passes on stream st: part holds marginal_workspace(nx, nk, nbatch) doubles, out
 // nbatch * (nx1 nk1 + nx2 nk2 + nx3 nk3 + nx1 nx2) doubles.  f nullptr: the item rows
 // are already in part (written by an observing x3 sweep); only the sums run.
 hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nbatch, const double hx[3],
@@ -140,9 +196,16 @@ hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nba
     a.s[1] = v[0] * v[2];
     a.s[2] = v[0] * v[1];
     a.s[3] = hx[2] * hk[0] * hk[1] * hk[2];
-    const long long total = ((long long)nx[0] * nk[0] + (long long)nx[1] * nk[1] + (long long)nx[2] * nk[2] +
-                             (long long)nx[0] * nx[1]) * nbatch;
-    hipLaunchKernelGGL(k_marg_sum, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part, a, out);
+    const long long nkp = (long long)nk[0] * nk[1] * nk[2], plane = (long long)nx[0] * nx[1];
+    const long long nw = (long long)nx[0] * nk[0] + (long long)nx[1] * nk[1] + (long long)nx[2] * nk[2];
+    a.chunks = marg_chunks(nx, nkp);
+    double* const axes = part + nitems * obs_row(nx[0], nx[1], nx[2]);
+    double* const cols = axes + nitems * marg_axes(nx);
+    hipLaunchKernelGGL(k_marg_axes, dim3((unsigned)nitems), dim3(256), 0, st, part, a, axes);
+    hipLaunchKernelGGL(k_marg_cols, dim3((unsigned)((plane + 255) / 256 * a.chunks * nbatch)), dim3(256), 0, st, part, a,
+                       cols);
+    hipLaunchKernelGGL(k_marg_sum, dim3((unsigned)((nw * nbatch + 3) / 4 + (plane * nbatch + 255) / 256)), dim3(256), 0, st,
+                       axes, cols, a, out);
     return hipGetLastError();
 }
 

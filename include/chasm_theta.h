@@ -18,7 +18,7 @@
  * zero padded), whatever the storage type of the field.  For nk 8 and 16 one block
  * holds an x-point's whole transform in LDS; for nk 32 and 64 (and on request 16) the
  * staged form runs the transforms over batches of x-points with a complex FP64
- * intermediate of 2 nk^3 values per x-point in device memory (at most about 2 GiB per
+ * intermediate of 2 nk^3 values per x-point in device memory (at most 192 MiB per
  * handle, plus nk^3 doubles per x-point of the batch for more than one nucleus).
  *
  * Field layout: as in chasm_advect.h, f[b][k3][k2][k1][x3][x2][x1] (x1 fastest),

@@ -47,7 +47,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 KERNEL_SOURCES = ["chasm_line.hpp", "chasm_kernels.hpp", "chasm_launch.hpp"]
 THETA_FLOPS_FILE = os.path.join(ROOT, "profiles", "theta_flops.json")
 THETA_SOURCES = ["chasm_theta.hip", "chasm_theta.hpp", "chasm_theta_plane.hpp", "chasm_theta_big.hpp",
-                 "chasm_theta_launch.hpp", "chasm_fft.hpp"]
+                 "chasm_theta_launch.hpp", "chasm_theta_table.hpp", "chasm_fft.hpp"]
 
 
 def kernel_digest(sources=KERNEL_SOURCES) -> str:

@@ -12,14 +12,17 @@
  * of eq. 4.10, kernel truncated at D = diam Omega), applied to the modulated data
  * e^{-2i (x - x_a).k} f and demodulated as in eq. 4.6:
  *   out(x, k_p) = sum_a z_a Theta^T_a[f](x, k_p).
+ * For real f that is one convolution with a real kernel, the sum over the nuclei of
+ * z_a T_q sin(2 (x - x_a).q), which is how it is evaluated.
  * The k-box Omega is the half-open grid box of side nk_d * hk_d; D is its diameter.
- * The library builds T and its transform on the host in FP64 once per handle and
- * evaluates the convolutions in FP64 on the device (FFT of period 2 nk per axis,
- * zero padded), whatever the storage type of the field.  For nk 8 and 16 one block
- * holds an x-point's whole transform in LDS; for nk 32 and 64 (and on request 16) the
- * staged form runs the transforms over batches of x-points with a complex FP64
- * intermediate of 2 nk^3 values per x-point in device memory (at most 192 MiB per
- * handle, plus nk^3 doubles per x-point of the batch for more than one nucleus).
+ * The library builds T on the host in FP64 once per handle and evaluates the
+ * convolutions in FP64 on the device (FFT of period 2 nk along k1 and k2, zero padded, and
+ * the product along k3), whatever the storage type of the field.  The kernel of a pair
+ * (x1, x2) takes 4 nk^3 doubles per nucleus: tables of up to 128 MiB (at least two pairs)
+ * are kept for the life of the handle, larger ones are made range by range in each call.
+ * For nk 8 and 16 one block holds an x-point's whole transform in LDS; for nk 32 and 64
+ * (and on request 16) the staged form runs the transforms over batches of x-points with a
+ * complex FP64 intermediate of nk^3 values per x-point in device memory (at most 192 MiB).
  *
  * Field layout: as in chasm_advect.h, f[b][k3][k2][k1][x3][x2][x1] (x1 fastest),
  * caller-owned contiguous device memory of float (CHASM_F32) or double (CHASM_F64).
@@ -61,9 +64,9 @@ typedef struct {
 } chasm_theta_desc;
 
 /* Create a handle: validates the descriptor (CHASM_EINVAL; CHASM_EUNSUPPORTED for
- * an nk without kernels), builds T and its transform in FP64 on the host, uploads the
- * transform and allocates one field-sized workspace (x-major copy) and, for the staged
- * form, its batch intermediate.  hip_stream is a
+ * an nk without kernels), builds T in FP64 on the host, uploads it and allocates one
+ * field-sized workspace (x-major copy), the kernel tables and, for the staged form, its
+ * batch intermediate.  hip_stream is a
  * hipStream_t (NULL = default stream) used by every later call. */
 chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, chasm_theta_t* out);
 

@@ -1,7 +1,7 @@
 // chasm_theta.hip -- C ABI of the truncated-kernel evaluation of Theta_V (Sec. 4):
-// descriptor validation, the FP64 tensor T of eq. 4.9 and its transform on the host,
-// kernel selection, and the apply sequence (transpose to x-major, per-x-point FFT
-// convolution, transpose back).  See include/chasm_theta.h.
+// descriptor validation, the FP64 tensor T of eq. 4.9 on the host, kernel selection, and
+// the apply sequence (transpose to x-major, kernel tables and convolutions over ranges of
+// x-points, transpose back).  See include/chasm_theta.h.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -127,37 +127,6 @@ static void tensor_positive(const int nk[3], const double hk[3], std::vector<dou
             }
 }
 
-// T placed circularly with period P_d = 2 nk_d (entries at |q_d| = nk_d are zero),
-// transformed along k1 and k2 only: B(xi1, xi2, q3) = sum_{q1, q2} T_q cos(2 pi (q1 xi1 /
-// P1 + q2 xi2 / P2)), real since T is even in each coordinate.  The full transform would
-// be That(xi) = sum_{|q3| < nk3} B(xi1, xi2, |q3|) e^{2 pi i q3 xi3 / P3}, so transforming
-// a zero-padded k3 line, multiplying by That and transforming back (without 1/P3) gives,
-// at the first nk3 outputs, o_j = sum_j' P3 B(xi1, xi2, |j - j'|) row_j'.  Output
-// kt[xi1][xi2][q3] = P3 B(xi1, xi2, q3), q3 < nk3 (q3 fastest), the order the kernel
-// reads it in.
-static void tensor_partial(const int nk[3], const std::vector<double>& T, std::vector<double>& kt)
-{
-    const int P[3] = {2 * nk[0], 2 * nk[1], 2 * nk[2]};
-    // per axis: g(xi) = g(0) + 2 sum_{q=1}^{nk-1} g(q) cos(2 pi q xi / P)
-    auto wcos = [&](int d, int q, int f) { return (q == 0 ? 1.0 : 2.0) * cos_turn((long long)q * f, P[d]); };
-    std::vector<double> B1((size_t)nk[2] * nk[1] * P[0]);   // [q3][q2][xi1]
-    for (int q3 = 0; q3 < nk[2]; ++q3)
-        for (int q2 = 0; q2 < nk[1]; ++q2)
-            for (int f1 = 0; f1 < P[0]; ++f1) {
-                double s = 0.0;
-                for (int q1 = 0; q1 < nk[0]; ++q1) s += T[((size_t)q3 * nk[1] + q2) * nk[0] + q1] * wcos(0, q1, f1);
-                B1[((size_t)q3 * nk[1] + q2) * P[0] + f1] = s;
-            }
-    kt.assign((size_t)P[0] * P[1] * nk[2], 0.0);
-    for (int q3 = 0; q3 < nk[2]; ++q3)
-        for (int f2 = 0; f2 < P[1]; ++f2)
-            for (int f1 = 0; f1 < P[0]; ++f1) {
-                double s = 0.0;
-                for (int q2 = 0; q2 < nk[1]; ++q2) s += B1[((size_t)q3 * nk[1] + q2) * P[0] + f1] * wcos(1, q2, f2);
-                kt[((size_t)f1 * P[1] + f2) * nk[2] + q3] = P[2] * s;
-            }
-}
-
 // The kernels of (dtype, nk), or nullptr.
 static const ThetaKernels* find_theta(int dtype, int nk)
 {
@@ -166,17 +135,51 @@ static const ThetaKernels* find_theta(int dtype, int nk)
     return k ? &k[dtype == CHASM_F64 ? 1 : 0] : nullptr;
 }
 
-// Staged form: x-points per batch (intermediate W of X * 2 nk^3 complex values) and whether
-// a handle uses it.  W of 192 MiB stays in the 256 MB memory-side cache between the
-// stages and is still three and a half rounds of one-wave blocks: 18^3 x 32^3 with two
-// nuclei takes 13.5 ms, against 14.5 at 2 GiB, 14.5 at 256 MiB, 14.0 at 128 and 16.0 at 64
-// (launch gaps and half-empty rounds).
-static long long big_batch(int nk, long long total)
+// How a handle goes through its x-points (order t, chasm_theta.hpp): the tables of at most
+// np pairs and, staged, an intermediate W of X x-points at a time.
+//   Tables: 4 nk^3 doubles per pair and nucleus, 128 MiB at most (two pairs at least).  If
+//   that holds all pairs they are made once, at create; else for each range of each call,
+//   which costs a pair as much as the Toeplitz products of one of its nx3 nbatch x-points.
+//   U, 2 nk^3 doubles per x1 node and nucleus, likewise.
+//   W: 192 MiB at most, which stays with the tables in the 256 MB memory-side cache between
+//   the stages: 18^3 x 32^3 with two nuclei takes 5.33 ms, against 5.44 at 256 MiB, 5.55 at
+//   128 and 6.45 at 64 (launch gaps and half-empty rounds).
+struct ThetaPlan {
+    bool big, resident, u_resident;
+    int np;
+    long long X;
+    size_t tab, U, W;                   // bytes
+};
+
+static bool use_big(const chasm_theta_desc* d, const ThetaKernels* ks);
+
+static ThetaPlan theta_plan(const chasm_theta_desc* d, const ThetaKernels* ks)
 {
-    const long long per = 2LL * nk * nk * nk * 16;
-    long long X = (192LL << 20) / per;
-    if (X < 1) X = 1;
-    return X < total ? X : total;
+    ThetaPlan p{};
+    p.big = use_big(d, ks);
+    const long long cube = (long long)d->nk[0] * d->nk[1] * d->nk[2];
+    const long long pairs = (long long)d->nx[0] * d->nx[1], m = (long long)d->nx[2] * d->nbatch;
+    const long long per_pair = 4 * cube * 8 * d->nnuc, per_node = 2 * cube * 8 * d->nnuc;
+    long long most = (128LL << 20) / per_pair;
+    if (most < 2) most = 2;
+    p.resident = most >= pairs;
+    const long long ranges = (pairs + most - 1) / most;
+    p.X = (pairs + ranges - 1) / ranges * m;            // ranges of equal size
+    if (p.big) {
+        const long long x = (192LL << 20) / (16 * cube);
+        if (x < p.X) p.X = x < 1 ? 1 : x;
+        if (p.X >= m) p.X -= p.X % m;                   // whole pairs
+    }
+    long long np = p.X >= m ? p.X / m : 2;
+    if (p.resident || np > pairs) np = pairs;
+    p.np = (int)np;
+    long long nodes = np / d->nx[1] + 2;                // x1 nodes of a range
+    p.u_resident = nodes >= d->nx[0] || per_node * d->nx[0] <= 128LL << 20;
+    if (p.u_resident) nodes = d->nx[0];
+    p.tab = (size_t)(np * per_pair);
+    p.U = (size_t)(nodes * per_node);
+    p.W = p.big ? (size_t)(p.X * cube * 16) : 0;
+    return p;
 }
 
 static bool use_big(const chasm_theta_desc* d, const ThetaKernels* ks)
@@ -192,13 +195,12 @@ struct chasm_theta_s {
     chasm_theta_desc desc;
     hipStream_t stream = nullptr;
     const ThetaKernels* ks = nullptr;
-    double* kt = nullptr;               // kernel transformed along k1, k2 (tensor_partial)
-    fft::cd* et = nullptr;              // modulation factors of the grid's nodes (k_theta_mod)
+    ThetaPlan plan{};
+    double* T = nullptr;                // tensor, [q1][q2][q3]
+    fft::cd* et = nullptr;              // factors of the grid's nodes (k_theta_mod)
+    double *tab = nullptr, *U = nullptr;   // kernel tables (chasm_theta_table.hpp) and their first sum
     void* ws = nullptr;
-    bool big = false;                   // staged form
-    long long X = 0;                    // x-points per batch of the staged form
-    fft::cd* W = nullptr;               // its complex intermediate
-    double* acc = nullptr;              // its sum over nuclei (more than one nucleus)
+    fft::cd* W = nullptr;               // complex intermediate of the staged form
     ThetaArgs args{};
     long long npts = 0, nkp = 0;
     bool poisoned = false;
@@ -249,15 +251,50 @@ static void desc_hk(const chasm_theta_desc* d, int nk[3], double hk[3])
     }
 }
 
+static hipError_t make_tables(chasm_theta_t h, const ThetaRange& r)
+{
+    int i1_0 = 0;
+    if (!h->plan.u_resident) {
+        const int nx2 = h->desc.nx[1];
+        i1_0 = r.p0 / nx2;
+        const hipError_t e = h->ks->node(h->U, h->T, h->et, h->args, i1_0, (r.p0 + r.np - 1) / nx2 - i1_0 + 1, h->stream);
+        if (e != hipSuccess) return e;
+    }
+    return h->ks->table(h->tab, h->U, h->et, h->args, r, i1_0, h->stream);
+}
+
+// The convolutions of all x-points on the x-major copy, range by range.
+static hipError_t convolve(chasm_theta_t h)
+{
+    const ThetaPlan& p = h->plan;
+    const long long m = (long long)h->desc.nx[2] * h->desc.nbatch, total = h->npts * h->desc.nbatch;
+    ThetaRange r{0, 0, 0, 0};
+    if (p.resident) r.np = p.np;
+    for (; r.t0 < total; r.t0 += p.X) {
+        r.n = total - r.t0 < p.X ? total - r.t0 : p.X;
+        hipError_t e = hipSuccess;
+        if (!p.resident) {
+            const int p0 = (int)(r.t0 / m), np = (int)((r.t0 + r.n - 1) / m) - p0 + 1;
+            const bool made = p0 == r.p0 && np == r.np;   // ranges within one pair
+            r.p0 = p0;
+            r.np = np;
+            if (!made) e = make_tables(h, r);
+        }
+        if (e == hipSuccess)
+            e = p.big ? h->ks->big(h->ws, h->tab, h->et, h->args, r, h->W, h->stream)
+                      : h->ks->theta(h->ws, h->tab, h->et, h->args, r, h->stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // x-major copy (mode_in), the convolutions on it, and back (mode_out); see TransposeMode.
 static chasm_status run_theta(chasm_theta_t h, int mode_in, const void* f, const void* g_in, double c_in, int mode_out,
                               void* out, const void* g_out, double c_out)
 {
     const int nb = h->desc.nbatch;
     hipError_t e = h->ks->transpose(mode_in, f, g_in, h->ws, h->nkp, h->npts, nb, c_in, h->stream);
-    if (e == hipSuccess)
-        e = h->big ? h->ks->big(h->ws, h->kt, h->et, h->args, h->W, h->acc, h->npts * nb, h->X, h->stream)
-                   : h->ks->theta(h->ws, h->kt, h->et, h->args, h->npts * nb, h->stream);
+    if (e == hipSuccess) e = convolve(h);
     if (e == hipSuccess) e = h->ks->transpose(mode_out, h->ws, g_out, out, h->npts, h->nkp, nb, c_out, h->stream);
     if (e != hipSuccess) {
         h->poisoned = true;
@@ -285,16 +322,10 @@ chasm_status chasm_theta_workspace_bytes(const chasm_theta_desc* desc, size_t* b
     if (!bytes) return tfail(CHASM_EINVAL, "bytes is NULL");
     const size_t es = desc->dtype == CHASM_F64 ? 8 : 4;
     const size_t pts = (size_t)desc->nx[0] * desc->nx[1] * desc->nx[2] * desc->nk[0] * desc->nk[1] * desc->nk[2];
-    const size_t P3 = (size_t)8 * desc->nk[0] * desc->nk[1] * desc->nk[2];
-    *bytes = pts * desc->nbatch * es + P3 * sizeof(double) + 512;
-    const size_t nrow = (size_t)desc->nx[0] + desc->nx[1] + desc->nx[2];
-    *bytes += (2 + (size_t)desc->nnuc * nrow) * desc->nk[0] * sizeof(fft::cd) + 256;
-    if (use_big(desc, ks)) {
-        const long long nk = desc->nk[0];
-        const long long X = big_batch((int)nk, (long long)desc->nx[0] * desc->nx[1] * desc->nx[2] * desc->nbatch);
-        *bytes += (size_t)X * 2 * nk * nk * nk * 16 + 256;
-        if (desc->nnuc > 1) *bytes += (size_t)X * nk * nk * nk * 8 + 256;
-    }
+    const ThetaPlan p = theta_plan(desc, ks);
+    const size_t nrow = (size_t)desc->nx[0] + desc->nx[1] + desc->nx[2], cube = (size_t)desc->nk[0] * desc->nk[1] * desc->nk[2];
+    *bytes = pts * desc->nbatch * es + cube * sizeof(double) + (4 + (size_t)desc->nnuc * nrow) * desc->nk[0] * sizeof(fft::cd) +
+             p.tab + p.U + p.W + 6 * 256;
     return CHASM_OK;
 }
 
@@ -329,9 +360,13 @@ chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, 
     int nk[3];
     double hk[3];
     desc_hk(desc, nk, hk);
-    std::vector<double> T, KT;
+    std::vector<double> T, TQ;
     tensor_positive(nk, hk, T);
-    tensor_partial(nk, T, KT);
+    TQ.resize(T.size());
+    for (int q3 = 0; q3 < nk[2]; ++q3)
+        for (int q2 = 0; q2 < nk[1]; ++q2)
+            for (int q1 = 0; q1 < nk[0]; ++q1)
+                TQ[((size_t)q1 * nk[1] + q2) * nk[2] + q3] = T[((size_t)q3 * nk[1] + q2) * nk[0] + q1];
 
     chasm_theta_s* h = new (std::nothrow) chasm_theta_s();
     if (!h) return tfail(CHASM_ENOMEM, "host allocation failed");
@@ -344,27 +379,23 @@ chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, 
         chasm_theta_destroy(h);
         return tfail(s, m);
     };
-    if (hipMalloc((void**)&h->kt, KT.size() * sizeof(double)) != hipSuccess)
-        return bail(CHASM_ENOMEM, "hipMalloc(symbol) failed");
-    if (hipMemcpyAsync(h->kt, KT.data(), KT.size() * sizeof(double), hipMemcpyHostToDevice, h->stream) !=
-        hipSuccess)
-        return bail(CHASM_EDEVICE, "symbol upload failed");
+    h->plan = theta_plan(desc, ks);
+    if (hipMalloc((void**)&h->T, TQ.size() * sizeof(double)) != hipSuccess)
+        return bail(CHASM_ENOMEM, "hipMalloc(tensor) failed");
+    if (hipMemcpyAsync(h->T, TQ.data(), TQ.size() * sizeof(double), hipMemcpyHostToDevice, h->stream) != hipSuccess)
+        return bail(CHASM_EDEVICE, "tensor upload failed");
     const size_t es = desc->dtype == CHASM_F64 ? 8 : 4;
     if (hipMalloc(&h->ws, (size_t)h->npts * h->nkp * desc->nbatch * es) != hipSuccess)
         return bail(CHASM_ENOMEM, "hipMalloc(workspace) failed");
-    h->big = use_big(desc, ks);
-    if (h->big) {
-        const long long nkk = nk[0];
-        h->X = big_batch(nk[0], h->npts * desc->nbatch);
-        if (hipMalloc((void**)&h->W, (size_t)h->X * 2 * nkk * nkk * nkk * sizeof(fft::cd)) != hipSuccess)
-            return bail(CHASM_ENOMEM, "hipMalloc(staged intermediate) failed");
-        if (desc->nnuc > 1 && hipMalloc((void**)&h->acc, (size_t)h->X * nkk * nkk * nkk * sizeof(double)) != hipSuccess)
-            return bail(CHASM_ENOMEM, "hipMalloc(staged accumulator) failed");
-    }
+    if (hipMalloc((void**)&h->tab, h->plan.tab) != hipSuccess || hipMalloc((void**)&h->U, h->plan.U) != hipSuccess)
+        return bail(CHASM_ENOMEM, "hipMalloc(kernel tables) failed");
+    if (h->plan.W && hipMalloc((void**)&h->W, h->plan.W) != hipSuccess)
+        return bail(CHASM_ENOMEM, "hipMalloc(staged intermediate) failed");
     ThetaArgs& a = h->args;
     a.npts = h->npts;
     a.nnuc = desc->nnuc;
-    const double P3 = 8.0 * nk[0] * nk[1] * nk[2];
+    a.nbatch = desc->nbatch;
+    const double PP = 4.0 * nk[0] * nk[1];
     for (int d = 0; d < 3; ++d) {
         a.nx[d] = desc->nx[d];
         a.x_lo[d] = desc->x_lo[d];
@@ -373,11 +404,15 @@ chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, 
     }
     for (int i = 0; i < desc->nnuc; ++i) {
         for (int d = 0; d < 3; ++d) a.xa[i][d] = desc->x_nuc[i][d];
-        a.wgt[i] = desc->z_nuc[i] * (2.0 / (M_PI * M_PI)) / P3;     // z_a 4/c_{3,1}, c_{3,1} = 2 pi^2; 1/P^3 of the inverse
+        a.wgt[i] = desc->z_nuc[i] * (2.0 / (M_PI * M_PI)) / (2.0 * PP);   // z_a 4/c_{3,1}, c_{3,1} = 2 pi^2; 1/P^2 of the inverse
     }
     if (hipMalloc((void**)&h->et, (size_t)mod_rows(a) * nk[0] * sizeof(fft::cd)) != hipSuccess)
-        return bail(CHASM_ENOMEM, "hipMalloc(modulation table) failed");
-    if (ks->mod(h->et, a, h->stream) != hipSuccess) return bail(CHASM_EDEVICE, "modulation table launch failed");
+        return bail(CHASM_ENOMEM, "hipMalloc(factors) failed");
+    if (ks->mod(h->et, a, h->stream) != hipSuccess) return bail(CHASM_EDEVICE, "factors launch failed");
+    if (h->plan.u_resident && ks->node(h->U, h->T, h->et, a, 0, desc->nx[0], h->stream) != hipSuccess)
+        return bail(CHASM_EDEVICE, "kernel table launch failed");
+    if (h->plan.resident && make_tables(h, ThetaRange{0, 0, 0, h->plan.np}) != hipSuccess)
+        return bail(CHASM_EDEVICE, "kernel table launch failed");
     if (hipStreamSynchronize(h->stream) != hipSuccess) return bail(CHASM_EDEVICE, "stream synchronize failed");
     *out = h;
     return CHASM_OK;
@@ -394,11 +429,12 @@ chasm_status chasm_theta_destroy(chasm_theta_t h)
 {
     if (!h) return CHASM_OK;
     if (h->stream) hipStreamSynchronize(h->stream);
-    if (h->kt) hipFree(h->kt);
+    if (h->T) hipFree(h->T);
+    if (h->tab) hipFree(h->tab);
+    if (h->U) hipFree(h->U);
     if (h->et) hipFree(h->et);
     if (h->ws) hipFree(h->ws);
     if (h->W) hipFree(h->W);
-    if (h->acc) hipFree(h->acc);
     delete h;
     return CHASM_OK;
 }

@@ -6,22 +6,30 @@
 #include "chasm_theta.hpp"
 #include "chasm_theta_big.hpp"
 #include "chasm_theta_plane.hpp"
+#include "chasm_theta_table.hpp"
 
 namespace chasm {
 
-// Compiled kernels: (storage type, nk) -> the one-block form (nk 8, 16) and the staged
-// form over batches of x-points (nk 16, 32, 64).
-using BigFn = hipError_t (*)(void* fx, const double* kt, const fft::cd* et, const ThetaArgs& a, fft::cd* W,
-                             double* acc, long long total, long long X, hipStream_t s);
+// x-points t0 .. t0 + n of a handle, and the range of its tables: pairs p0 .. p0 + np.
+struct ThetaRange {
+    long long t0, n;
+    int p0, np;
+};
 
+// Compiled kernels: (storage type, nk) -> the one-block form (nk 8, 16) and the staged
+// form (nk 16, 32, 64) on a range of x-points, and the tables of a range of pairs.
 struct ThetaKernels {
     int dtype, nk;
-    hipError_t (*theta)(void* fx, const double* kt, const fft::cd* et, const ThetaArgs& a, long long total,
+    hipError_t (*theta)(void* fx, const double* tab, const fft::cd* et, const ThetaArgs& a, const ThetaRange& r,
                         hipStream_t s);
     hipError_t (*transpose)(int mode, const void* in, const void* g, void* out, long long rows, long long cols,
                             int batch, double c, hipStream_t s);
-    BigFn big;                 // staged form (nullptr: none)
+    hipError_t (*big)(void* fx, const double* tab, const fft::cd* et, const ThetaArgs& a, const ThetaRange& r, fft::cd* W,
+                      hipStream_t s);   // nullptr: none
     hipError_t (*mod)(fft::cd* et, const ThetaArgs& a, hipStream_t s);
+    hipError_t (*node)(double* U, const double* T, const fft::cd* et, const ThetaArgs& a, int i1_0, int n1, hipStream_t s);
+    hipError_t (*table)(double* tab, const double* U, const fft::cd* et, const ThetaArgs& a, const ThetaRange& r, int i1_0,
+                        hipStream_t s);
 };
 
 template <typename K>
@@ -35,19 +43,20 @@ long long resident(K k, int threads)
 }
 
 template <typename T, int NK>
-hipError_t launch_theta(void* fx, const double* kt, const fft::cd* et, const ThetaArgs& a, long long total,
-                               hipStream_t s)
+hipError_t launch_theta(void* fx, const double* tab, const fft::cd* et, const ThetaArgs& a, const ThetaRange& r,
+                        hipStream_t s)
 {
     auto k = k_theta<T, NK>;
     constexpr int NT = NK * NK;
-    const long long res = resident(k, NT);
-    const unsigned grid = (unsigned)(res > 0 && res < total ? res : total);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(NT), 0, s, static_cast<T*>(fx), kt, et, a, total);
+    const long long res = resident(k, NT) / 8 * 8;
+    const unsigned grid = (unsigned)(res > 0 && res < r.n ? res : r.n);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(NT), 0, s, static_cast<T*>(fx), tab, et, a, (unsigned)r.t0, (unsigned)r.n,
+                       (unsigned)r.p0);
     return hipGetLastError();
 }
 
-// The modulation table of a handle (k_theta_mod): rows of nk factors.
-inline long long mod_rows(const ThetaArgs& a) { return 2 + (long long)a.nnuc * (a.nx[0] + a.nx[1] + a.nx[2]); }
+// The factors of a handle (k_theta_mod): rows of nk.
+inline long long mod_rows(const ThetaArgs& a) { return 4 + (long long)a.nnuc * (a.nx[0] + a.nx[1] + a.nx[2]); }
 
 template <int NK>
 hipError_t launch_mod(fft::cd* et, const ThetaArgs& a, hipStream_t s)
@@ -57,29 +66,38 @@ hipError_t launch_mod(fft::cd* et, const ThetaArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// Staged form: x-points in batches of X; per batch and nucleus the three stages.
+// U of the nodes i1_0 .. i1_0 + n1, and the tables of a range from U of the nodes i1_0 ..
+template <int NK>
+hipError_t launch_node(double* U, const double* T, const fft::cd* et, const ThetaArgs& a, int i1_0, int n1, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_theta_u<NK>, dim3((unsigned)n1 * a.nnuc, 2 * NK / 4), dim3(256), 0, s, U, T, et, a, i1_0);
+    return hipGetLastError();
+}
+
+template <int NK>
+hipError_t launch_table(double* tab, const double* U, const fft::cd* et, const ThetaArgs& a, const ThetaRange& r, int i1_0,
+                        hipStream_t s)
+{
+    hipLaunchKernelGGL(k_theta_table<NK>, dim3((unsigned)r.np * a.nnuc, NK / 4), dim3(256), 0, s, tab, U, et, a, r.p0, i1_0,
+                       NK < 32 ? NK : 32);
+    return hipGetLastError();
+}
+
 template <typename T, int NK>
-hipError_t launch_big(void* fx, const double* kt, const fft::cd* et, const ThetaArgs& a, fft::cd* W,
-                             double* acc, long long total, long long X, hipStream_t s)
+hipError_t launch_big(void* fx, const double* tab, const fft::cd* et, const ThetaArgs& a, const ThetaRange& r, fft::cd* W,
+                      hipStream_t s)
 {
     using B = BigShape<NK>;
-    for (long long x0 = 0; x0 < total; x0 += X) {
-        const long long nb = total - x0 < X ? total - x0 : X;
-        for (int nu = 0; nu < a.nnuc; ++nu) {
-            hipLaunchKernelGGL((k_thA<T, NK>), dim3((unsigned)(nb * NK * NK / B::LA)), dim3(B::LA), 0, s,
-                               static_cast<const T*>(fx), W, et, a, x0, nu);
-            if constexpr (NK <= 32)
-                hipLaunchKernelGGL((k_thBCD_plane<NK>), dim3((unsigned)(nb * B::P * 2 * NK / 64)), dim3(64), 0, s, W, kt,
-                                   et, a, x0, nu);
-            else
-                hipLaunchKernelGGL((k_thBCD<NK>), dim3((unsigned)(nb * B::P)), dim3(B::NTB), 0, s, W, kt, et, a, x0, nu);
-            hipLaunchKernelGGL((k_thE<T, NK>), dim3((unsigned)(nb * NK * NK / B::LE)), dim3(B::LE), 0, s, W, acc,
-                               static_cast<T*>(fx), et, a, x0, nu, nu == 0 ? 1 : 0, nu == a.nnuc - 1 ? 1 : 0);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-    }
-    return hipSuccess;
+    const unsigned t0 = (unsigned)r.t0, p0 = (unsigned)r.p0, planes = (unsigned)(r.n * NK);
+    hipLaunchKernelGGL((k_thA<T, NK>), dim3((unsigned)(r.n * NK * NK / B::LA)), dim3(B::LA), 0, s,
+                       static_cast<const T*>(fx), W, a, t0);
+    if constexpr (NK <= 32)
+        hipLaunchKernelGGL((k_thBCD_plane<NK>), dim3(planes * 2 * NK / 64), dim3(64), 0, s, W, tab, et, a, t0, p0);
+    else
+        hipLaunchKernelGGL((k_thBCD<NK>), dim3(planes), dim3(B::NTB), 0, s, W, tab, et, a, t0, p0);
+    hipLaunchKernelGGL((k_thE<T, NK>), dim3((unsigned)(r.n * NK * NK / B::LE)), dim3(B::LE), 0, s, W,
+                       static_cast<T*>(fx), a, t0);
+    return hipGetLastError();
 }
 
 template <typename T>

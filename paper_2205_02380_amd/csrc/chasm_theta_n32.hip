@@ -4,8 +4,8 @@
 namespace chasm {
 
 static const ThetaKernels kKernels[2] = {
-    {0, 32, nullptr, launch_transpose<float>, launch_big<float, 32>, launch_mod<32>},
-    {1, 32, nullptr, launch_transpose<double>, launch_big<double, 32>, launch_mod<32>},
+    {0, 32, nullptr, launch_transpose<float>, launch_big<float, 32>, launch_mod<32>, launch_node<32>, launch_table<32>},
+    {1, 32, nullptr, launch_transpose<double>, launch_big<double, 32>, launch_mod<32>, launch_node<32>, launch_table<32>},
 };
 
 const ThetaKernels* theta_kernels_32() { return kKernels; }

@@ -4,8 +4,8 @@
 namespace chasm {
 
 static const ThetaKernels kKernels[2] = {
-    {0, 64, nullptr, launch_transpose<float>, launch_big<float, 64>, launch_mod<64>},
-    {1, 64, nullptr, launch_transpose<double>, launch_big<double, 64>, launch_mod<64>},
+    {0, 64, nullptr, launch_transpose<float>, launch_big<float, 64>, launch_mod<64>, launch_node<64>, launch_table<64>},
+    {1, 64, nullptr, launch_transpose<double>, launch_big<double, 64>, launch_mod<64>, launch_node<64>, launch_table<64>},
 };
 
 const ThetaKernels* theta_kernels_64() { return kKernels; }

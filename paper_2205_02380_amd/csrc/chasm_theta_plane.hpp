@@ -1,23 +1,21 @@
-// chasm_theta_plane.hpp -- the (k2, k3) part of the truncated-kernel convolution of
-// Theta_V on one (x, xi1) plane by 2 N_k lanes of one wave, and the one-block kernel
-// built on it (N_k = 8 and 16).  Mathematics and notation as in chasm_theta.hpp.
+// chasm_theta_plane.hpp -- the (k2, k3) part of the convolution of Theta_V on one
+// (x, xi1) plane by 2 N_k lanes of one wave, and the one-block kernel built on it
+// (N_k = 8 and 16).  Mathematics and notation as in chasm_theta.hpp.
 //
 // A plane is N_k rows (k3) of N_k complex values (k2).  Its work is
 //   B  per row: k2 forward transform, zero-padded to P = 2 N_k outputs xi2 = 2 f + h:
 //      the N_k-point transform of row_j w^{h j}, h = 0, 1;
-//   C  per xi2: the N_k x N_k real symmetric Toeplitz product along k3;
+//   C  per xi2: the even and the odd N_k x N_k real Toeplitz matrix along k3;
 //   D  per row: k2 inverse, first N_k outputs: the sum over h of the N_k-point inverse of
 //      the xi2 = 2 f + h inputs times w^{-h j}.
 // Lane (h, k3) does B and D of row k3 for its h, and C of line xi2 = 2 k3 + h, so all
 // 2 N_k lanes are busy in every stage with one N_k-point line each (2 N_k VGPR pairs).
 // Only lanes of one wave share a plane, so nothing but the two transposes between rows
 // and lines orders them: those go through the plane's own LDS slot, real parts and then
-// imaginary parts (K is real, so the two parts of C are independent), 2 N_k lines of
-// N_k doubles -- exactly the slot's size.  The sum over h exchanges half of each line
-// with the partner lane, after which each lane holds N_k/2 outputs of its row.
-// The factors that a lane needs for its own h (twiddles with the modulation along k2
-// folded in) are held one or two to a lane and broadcast within rows of 16 lanes
-// (LineFactors).
+// imaginary parts, 2 N_k lines of N_k doubles -- exactly the slot's size.  The sum over h
+// exchanges half of each line with the partner lane, after which each lane holds N_k/2
+// outputs of its row.  The factors w^{h j} of a lane's own h are held one or two to a lane
+// and broadcast within rows of 16 lanes (LineFactors).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -106,80 +104,167 @@ struct LineFactors<8> {
     __device__ __forceinline__ void renew() {}
 };
 
-// o = K x for the symmetric Toeplitz matrix K[j][i] = kk[|j - i|], JB outputs at a time
-// (bounds the accumulators).
+// The kernel of a line (xi1, xi2) at an x-point: of each nucleus the lane's table line
+// (chasm_theta_table.hpp), and the x-point's row e^{-i phi_3 q}, the same for all lanes.
+struct KernelLine {
+    const double* tab;
+    long long tab_nu;            // from one nucleus to the next
+    const fft::cd* e3;
+    long long e3_nu;
+    int nnuc;
+};
+
+// D and S of nucleus nu.
 template <int NK>
-__device__ __forceinline__ void toeplitz_line(const double (&kk)[NK], double* line)
+__device__ __forceinline__ void load_kernel(const KernelLine& kl, int nu, double (&D)[NK], double (&S)[NK])
 {
-    constexpr int JB = 8;
-    double x[NK];
-    fft::sfor<0, NK>([&](auto ic) { x[decltype(ic)::value] = line[decltype(ic)::value]; });
-    fft::sfor<0, NK / JB>([&](auto bc) {
-        constexpr int j0 = decltype(bc)::value * JB;
-        double o[JB];
-        fft::sfor<0, JB>([&](auto jc) { o[decltype(jc)::value] = 0.0; });
-        fft::sfor<0, NK>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            fft::sfor<0, JB>([&](auto jc) {
-                constexpr int j = j0 + decltype(jc)::value;
-                constexpr int d = j > i ? j - i : i - j;
-                o[j - j0] = fma(kk[d], x[i], o[j - j0]);
-            });
+    const double2* p = reinterpret_cast<const double2*>(kl.tab + nu * kl.tab_nu);
+    fft::sfor<0, NK / 2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        const double2 d = p[q * 2 * NK], s = p[(q + NK / 2) * 2 * NK];
+        D[2 * q] = d.x;
+        D[2 * q + 1] = d.y;
+        S[2 * q] = s.x;
+        S[2 * q + 1] = s.y;
+    });
+}
+
+// From D and S of the first nucleus, D(q) = sum_a D_a cos(phi_3 q), S(q) = sum_a S_a sin(phi_3 q).
+template <int NK>
+__device__ __forceinline__ void kernel_values(const KernelLine& kl, double (&D)[NK], double (&S)[NK])
+{
+    using namespace fft;
+    sfor<0, NK>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        const cd e = kl.e3[q];
+        D[q] *= e.re;
+        S[q] *= -e.im;
+    });
+#pragma unroll 1
+    for (int nu = 1; nu < kl.nnuc; ++nu) {
+        double d[NK], s[NK];
+        load_kernel<NK>(kl, nu, d, s);
+        const cd* e3 = kl.e3 + nu * kl.e3_nu;
+        sfor<0, NK>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            const cd e = e3[q];
+            D[q] = fma(d[q], e.re, D[q]);
+            S[q] = fma(s[q], -e.im, S[q]);
         });
-        fft::sfor<0, JB>([&](auto jc) { line[j0 + decltype(jc)::value] = o[decltype(jc)::value]; });
+    }
+}
+
+// (gr, gi) <- 2 (S gr + D gi, S gi - D gr), D the even and S the odd Toeplitz matrix of the
+// given values.  With J the reversal, J D J = D and J S J = -S: on the even and odd parts
+// e_i = x_i + x_{N-1-i}, o_i = x_i - x_{N-1-i}, i < N/2, D is one N/2 x N/2 matrix each, of
+// entries D(j - i) +- D(N-1-i-j), and S carries o to e and e to o with S(j - i) +- S(N-1-i-j).
+// That is half the products; the entries serve both parts of the line, and by symmetry
+// the two of (i, j) and (j, i): 0.70 of the operations of four full products at N = 16.
+template <int N>
+__device__ __forceinline__ void toeplitz_line(const double (&D)[N], const double (&S)[N], double (&gr)[N], double (&gi)[N])
+{
+    using namespace fft;
+    constexpr int H = N / 2;
+    auto butterfly = [](double (&g)[N]) {
+        sfor<0, H>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const double a = g[i], b = g[N - 1 - i];
+            g[i] = a + b;
+            g[N - 1 - i] = a - b;
+        });
+    };
+    butterfly(gr);
+    butterfly(gi);
+    double re[N], im[N];
+    sfor<0, N>([&](auto ic) { re[decltype(ic)::value] = im[decltype(ic)::value] = 0.0; });
+    // the even part of output j is in [j], its odd part in [N - 1 - j]
+    constexpr int B = H < 8 ? H : 8;     // tiles of B x B entries: fewer registers live at a time
+    sfor<0, H * H>([&](auto tc) {
+        constexpr int t = decltype(tc)::value, tile = t / (B * B), in = t % (B * B);
+        constexpr int j = tile / (H / B) * B + in / B, i = tile % (H / B) * B + in % B;
+        if constexpr (i <= j) {
+            const std::integral_constant<int, j> jc;
+            const std::integral_constant<int, i> ic;
+            constexpr int d = j - i, c = N - 1 - i - j;
+            const double p = D[d] + D[c], m = D[d] - D[c];
+            auto even = [&](auto oc, auto nc) {
+                constexpr int o = decltype(oc)::value, n = decltype(nc)::value;
+                re[o] = fma(p, gi[n], re[o]);
+                im[o] = fma(-p, gr[n], im[o]);
+                re[N - 1 - o] = fma(m, gi[N - 1 - n], re[N - 1 - o]);
+                im[N - 1 - o] = fma(-m, gr[N - 1 - n], im[N - 1 - o]);
+            };
+            auto odd = [&](double sp, double sm, auto oc, auto nc) {
+                constexpr int o = decltype(oc)::value, n = decltype(nc)::value;
+                re[o] = fma(sp, gr[N - 1 - n], re[o]);
+                im[o] = fma(sp, gi[N - 1 - n], im[o]);
+                re[N - 1 - o] = fma(sm, gr[n], re[N - 1 - o]);
+                im[N - 1 - o] = fma(sm, gi[n], im[N - 1 - o]);
+            };
+            even(jc, ic);
+            if constexpr (d > 0) {
+                even(ic, jc);
+                const double sp = S[d] + S[c], sm = S[d] - S[c];
+                odd(sp, sm, jc, ic);
+                odd(-sm, -sp, ic, jc);
+            } else {
+                odd(S[c], -S[c], jc, ic);
+            }
+        }
+    });
+    sfor<0, H>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        gr[j] = re[j] + re[N - 1 - j];
+        gr[N - 1 - j] = re[j] - re[N - 1 - j];
+        gi[j] = im[j] + im[N - 1 - j];
+        gi[N - 1 - j] = im[j] - im[N - 1 - j];
     });
 }
 
 // Stages B, C, D of the plane in `slot`, in place.  k3, h: this lane's row and half;
-// kt: the kernel values K(xi1, 2 k3 + h, 0 .. N_k - 1) of this lane's line; tw: the factors
-// of this lane's half, row_j -> row_j tw_j before B and out_j -> conj(tw_j) out_j after D.
+// kl: the kernel of this lane's line xi2 = 2 k3 + h; tw: the factors w^{h j} of this lane's
+// half.
 template <int NK>
-__device__ __forceinline__ void plane_conv(fft::cd* slot, const double* __restrict__ kt, LineFactors<NK>& tw, int k3,
-                                           int h)
+__device__ __forceinline__ void plane_conv(fft::cd* slot, const KernelLine& kl, LineFactors<NK>& tw, int k3, int h)
 {
     using namespace fft;
     using S = PlaneShape<NK>;
-    // the plane's row and the kernel values are all requested before the first use of any
-    // (left to itself the compiler reads the row one value at a time)
-    cd y[NK];
     cd* row = slot + k3 * S::RS;
-    sfor<0, NK>([&](auto jc) { y[decltype(jc)::value] = row[decltype(jc)::value]; });
-    double kk[NK];
-    auto kernel_values = [&] {
-        const double2* kr = reinterpret_cast<const double2*>(kt);
-        sfor<0, NK / 2>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            const double2 t = kr[q];
-            kk[2 * q] = t.x;
-            kk[2 * q + 1] = t.y;
-        });
-    };
-    if constexpr (NK < 32) kernel_values();
-    __builtin_amdgcn_sched_barrier(0);
-    sfor<0, NK>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        y[j] = cmul(y[j], tw.template at<j>());
-    });
-    tw.renew();
-    transform<NK, -1>(y);
-    // at N_k = 32 the line alone takes 128 registers: with the kernel values loaded ahead the
-    // transform spilled (18^3 x 32^3, two nuclei: 13.4 ms, against 12.5 with them after it)
-    if constexpr (NK >= 32) {
-        __builtin_amdgcn_sched_barrier(0);
-        kernel_values();
-    }
-    wave_order();
+    double gr[NK], gi[NK];
     double* col = reinterpret_cast<double*>(slot) + h * NK * S::RS + k3;      // row k3 of half h: stride RS
     double* line = reinterpret_cast<double*>(slot) + (h * NK + k3) * S::RS;   // line xi2 = 2 k3 + h
-    sfor<0, NK>([&](auto fc) { col[decltype(fc)::value * S::RS] = y[decltype(fc)::value].re; });
+    double kd[NK], ks[NK];
+    {
+        cd y[NK];
+        // requested before the first use of any (left to itself the compiler reads the row
+        // one value at a time)
+        sfor<0, NK>([&](auto jc) { y[decltype(jc)::value] = row[decltype(jc)::value]; });
+        load_kernel<NK>(kl, 0, kd, ks);
+        __builtin_amdgcn_sched_barrier(0);
+        sfor<0, NK>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            y[j] = cmul(y[j], tw.template at<j>());
+        });
+        tw.renew();
+        transform<NK, -1>(y);
+        wave_order();
+        sfor<0, NK>([&](auto fc) { col[decltype(fc)::value * S::RS] = y[decltype(fc)::value].re; });
+        wave_order();
+        sfor<0, NK>([&](auto ic) { gr[decltype(ic)::value] = line[decltype(ic)::value]; });
+        wave_order();
+        sfor<0, NK>([&](auto fc) { col[decltype(fc)::value * S::RS] = y[decltype(fc)::value].im; });
+        wave_order();
+        sfor<0, NK>([&](auto ic) { gi[decltype(ic)::value] = line[decltype(ic)::value]; });
+    }
+    kernel_values<NK>(kl, kd, ks);
+    toeplitz_line<NK>(kd, ks, gr, gi);
+    cd y[NK];
     wave_order();
-    toeplitz_line<NK>(kk, line);
+    sfor<0, NK>([&](auto ic) { line[decltype(ic)::value] = gr[decltype(ic)::value]; });
     wave_order();
     sfor<0, NK>([&](auto fc) { y[decltype(fc)::value].re = col[decltype(fc)::value * S::RS]; });
     wave_order();
-    sfor<0, NK>([&](auto fc) { col[decltype(fc)::value * S::RS] = y[decltype(fc)::value].im; });
-    wave_order();
-    toeplitz_line<NK>(kk, line);
+    sfor<0, NK>([&](auto ic) { line[decltype(ic)::value] = gi[decltype(ic)::value]; });
     wave_order();
     sfor<0, NK>([&](auto fc) { y[decltype(fc)::value].im = col[decltype(fc)::value * S::RS]; });
     wave_order();
@@ -196,178 +281,115 @@ __device__ __forceinline__ void plane_conv(fft::cd* slot, const double* __restri
     });
 }
 
-// Modulation table of a handle: the P factors w^j = e^{-2 pi i j / P}, then for every
-// nucleus the rows e^{-i phi k} (k < N_k, phi = 2 (x - x_a) hk) of the nx1 + nx2 + nx3
-// nodes of the three axes.  One thread per (row of N_k factors, k).
+// The factors w^{h j} of a half line, as LineFactors for lane `lane` of the block (lds:
+// N_k = 8 only, the table [h][j] with rows of 9, written by this call).
 template <int NK>
-__global__ __launch_bounds__(256) void k_theta_mod(fft::cd* __restrict__ et, const ThetaArgs a)
-{
-    const int nrow = a.nx[0] + a.nx[1] + a.nx[2];
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (long long)NK * (2 + (long long)a.nnuc * nrow)) return;
-    const int k = (int)(t % NK);
-    const long long r = t / NK;
-    double ph;
-    if (r < 2) {
-        ph = 3.14159265358979323846 * (double)t / NK;
-    } else {
-        const int nu = (int)((r - 2) / nrow);
-        int i = (int)((r - 2) % nrow), d = 0;
-        while (d < 2 && i >= a.nx[d]) i -= a.nx[d++];
-        const double xc = a.x_lo[d] + i * a.hx[d];
-        ph = 2.0 * (xc - a.xa[nu][d]) * a.hk[d] * k;
-    }
-    double s, c;
-    sincos(ph, &s, &c);
-    et[t] = fft::cd{c, -s};
-}
-
-// The rows of the modulation table at x-point xp (batch members stacked) for nucleus nu.
-struct ModRows {
-    const fft::cd *e1, *e2, *e3;
-};
-
-template <int NK>
-__device__ __forceinline__ ModRows mod_rows_at(const fft::cd* et, const ThetaArgs& a, long long xp, int nu)
-{
-    const unsigned loc = (unsigned)(xp % (unsigned)a.npts);
-    const unsigned i1 = loc % (unsigned)a.nx[0], up = loc / (unsigned)a.nx[0];
-    const unsigned i2 = up % (unsigned)a.nx[1], i3 = up / (unsigned)a.nx[1];
-    const fft::cd* e = et + 2 * NK + (long long)nu * (a.nx[0] + a.nx[1] + a.nx[2]) * NK;
-    return {e + i1 * NK, e + (a.nx[0] + i2) * NK, e + (a.nx[0] + a.nx[1] + i3) * NK};
-}
-
-// Factors of a half line: entry j = e2_j w^{h j}, as LineFactors for lane `lane` of the
-// block (lds: N_k = 8 only, the table [h][j] with rows of 9, written by this call).
-template <int NK>
-__device__ __forceinline__ LineFactors<NK> half_factors(const fft::cd* et, const fft::cd* e2, int h, int lane, fft::cd* lds)
+__device__ __forceinline__ LineFactors<NK> half_factors(const fft::cd* et, int h, int lane, fft::cd* lds)
 {
     using namespace fft;
     if constexpr (NK == 8) {
         const int hh = (lane / 8) & 1, j = lane % 8;
-        lds[hh * 9 + j] = hh ? cmul(e2[j], et[j]) : e2[j];
+        lds[hh * 9 + j] = hh ? et[2 * j] : cd{1.0, 0.0};
         return {lds + h * 9};
     } else {
         LineFactors<NK> f;
         sfor<0, NK / 16>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
-            const int j = lane % 16 + 16 * q;
-            f.v[q] = h ? cmul(e2[j], et[j]) : e2[j];
+            f.v[q] = h ? et[2 * (lane % 16 + 16 * q)] : cd{1.0, 0.0};
         });
         return f;
     }
 }
 
-// One x-point per block at a time (persistent over x-points), N_k^2 threads, FP64
-// throughout.  The xi1 axis goes by residue: chunk r < R holds xi1 = r + R m, m < C = 8
-// (R C = P), the C-point transform of line_j e^{-i phi_1 j} w^{r j} folded modulo C.  Per
-// chunk:
-//   A  thread (k2, k3): modulated k1 line, C-point transform        -> plane m, [k3][k2]
-//   BCD  plane_conv on the C planes, 2 N_k lanes each
-//   E  thread (k2, k3): C-point inverse over the planes, demodulated, into the real
-//      result the thread keeps in registers (16 doubles at N_k = 16)
-// The modulations are products of per-axis factors: a thread forms e^{-i phi_1 j} w^{r j}
-// e^{-i phi_3 k3} for its own j = k2 and broadcasts it along its line's row of lanes, for A
-// and, conjugated, for E; the k2 factor rides on the twiddles of B and D.
-//
-// Bound: FP64 VALU (1.35e6 lane instructions per x-point at N_k = 16, 39 % of them the
-// Toeplitz products; 72 % VALU busy) beside 1.1 MB of LDS traffic per x-point.  The planes
-// of a chunk take 35 KB at N_k = 16; three blocks (three waves per SIMD, 168 VGPRs) share a
-// CU, and one's barriers and LDS waits hide behind the others.  The loads whose latency
-// showed (the row of a plane, its kernel values, the line of the next chunk) are issued
-// together ahead of their use.  Measured on 61^3 x 16^3, FP32 field: 13.9 ms; 14.7 ms with
-// two chunks of 16 planes, LDS factor tables and two waves per SIMD; 22.1 ms for a form
-// with the k2-transformed planes side by side in LDS (140 KB, one wave per SIMD, a barrier
-// after every stage).
+// One x-point per block at a time (persistent over the x-points t0 .. t0 + count, whose
+// first pair is p0), N_k^2 threads, FP64 throughout:
+//   A  thread (k2, k3): k1 line times e^{-2 pi i j / (4 N_k)}, N_k-point transform: plane c
+//      is xi1 = 2 c + 1/2                                    -> plane c, [k3][k2]
+//   BCD  plane_conv on the N_k planes, 2 N_k lanes each
+//   E  thread (k2, k3): N_k-point inverse over the planes; the real part, demodulated.
+// Each XCD takes a contiguous share of the x-points, so that the points of a pair find its
+// table lines (131 KB at N_k = 16) in one L2.
+// Bound: FP64 VALU (66 % busy at N_k = 16) beside 0.6 MB of LDS traffic per x-point; two
+// waves per SIMD with 233 registers, all planes of an x-point in LDS (70 KB), so that two
+// barriers separate the stages.  Measured on 61^3 x 16^3, FP32 field, one nucleus: 8.1 ms
+// (and 0.2 of tables); 13.9 ms for full complex spectra of the modulated field, which has
+// twice the planes, a modulation on every line and one pass per nucleus.
 template <typename T, int NK>
-__global__ __launch_bounds__(NK * NK, NK == 16 ? 3 : 4) void k_theta(T* __restrict__ fx, const double* __restrict__ kt,
+__global__ __launch_bounds__(NK * NK, NK == 16 ? 2 : 3) void k_theta(T* __restrict__ fx, const double* __restrict__ tab,
                                                                     const fft::cd* __restrict__ et, const ThetaArgs a,
-                                                                    long long total)
+                                                                    unsigned t0, unsigned count, unsigned p0)
 {
     using namespace fft;
     using S = PlaneShape<NK>;
-    constexpr int NT = NK * NK, P = S::P, RS = S::RS, C = 8, R = P / C;
+    constexpr int NT = NK * NK, P = S::P, RS = S::RS;
     constexpr int GROUPS = NT / S::LANES;            // planes worked on at a time
-    static_assert(C % GROUPS == 0, "whole rounds");
-    constexpr bool TAB = NK == 8;                    // factors through LDS (see LineFactors)
-    __shared__ cd W[C * S::SLOT];
-    __shared__ cd TW[TAB ? 2 * 9 : 1], E02[TAB ? NK * 9 : 1];
+    static_assert(NK % GROUPS == 0, "whole rounds");
+    __shared__ cd W[NK * S::SLOT];
+    __shared__ cd TW[NK == 8 ? 2 * 9 : 1];
 
     const int tid = threadIdx.x;
     const int c2 = tid % NK, c3 = tid / NK;          // k1 line (k2, k3) of stages A and E
     const int k3 = tid % NK, h = (tid / NK) & 1, grp = tid / S::LANES;
-    const cd wj = et[c2];                            // w^j, j = c2
+    LineFactors<NK> tw = half_factors<NK>(et, h, tid, TW);
 
-    for (long long xp = blockIdx.x; xp < total; xp += gridDim.x) {
-        T* line = fx + xp * (long long)(NK * NK * NK) + tid * NK;
-        double th[NK];
-        sfor<0, NK>([&](auto jc) { th[decltype(jc)::value] = 0.0; });
-        T fv[NK];
-        load_raw<T, NK>(line, fv);
-
-        for (int nu = 0; nu < a.nnuc; ++nu) {
-            const ModRows e = mod_rows_at<NK>(et, a, xp, nu);
-            const double w = a.wgt[nu];
-            if constexpr (TAB) __syncthreads();      // the previous pass no longer reads the tables
-            LineFactors<NK> tw = half_factors<NK>(et, e.e2, h, tid, TW);
-            cd m02 = cmul(e.e1[c2], e.e3[c3]);       // entry j = c2 of this line's factors
-#pragma unroll 1
-            for (int r = 0; r < R; ++r) {
-                LineFactors<NK> lf;
-                if constexpr (TAB) {
-                    E02[c3 * 9 + c2] = m02;
-                    lf.v = E02 + c3 * 9;
-                    __syncthreads();
-                } else {
-                    lf.v[0] = m02;
-                }
-                {   // A
-                    cd y[C];
-                    sfor<0, NK>([&](auto jc) {
-                        constexpr int j = decltype(jc)::value;
-                        const cd m = lf.template at<j>();
-                        const double f = (double)fv[j];
-                        if constexpr (j < C) y[j] = cd{m.re * f, m.im * f};
-                        else y[j % C] = cd{fma(m.re, f, y[j % C].re), fma(m.im, f, y[j % C].im)};
-                    });
-                    transform<C, -1>(y);
-                    sfor<0, C>([&](auto mc) {
-                        constexpr int m = decltype(mc)::value;
-                        W[m * S::SLOT + c3 * RS + c2] = y[m];
-                    });
-                }
-                __syncthreads();
-#pragma unroll 1
-                for (int m = grp; m < C; m += GROUPS)   // B, C, D: xi1 = r + R m, xi2 = 2 k3 + h
-                    plane_conv<NK>(W + m * S::SLOT, kt + ((long long)(r + R * m) * P + 2 * k3 + h) * NK, tw, k3, h);
-                __syncthreads();
-                // the weight rides on E's factors; m02 moves on to the next chunk
-                if constexpr (!TAB) lf.v[0] = cd{w * m02.re, w * m02.im};
-                lf.renew();
-                m02 = cmul(m02, wj);
-                {   // E
-                    load_raw<T, NK>(line, fv);       // for the next chunk's A, ahead of its first use
-                    __builtin_amdgcn_sched_barrier(0);
-                    cd y[C];
-                    sfor<0, C>([&](auto mc) {
-                        constexpr int m = decltype(mc)::value;
-                        y[m] = W[m * S::SLOT + c3 * RS + c2];
-                    });
-                    transform<C, +1>(y);
-                    if constexpr (TAB) sfor<0, C>([&](auto mc) {
-                        y[decltype(mc)::value].re *= w;
-                        y[decltype(mc)::value].im *= w;
-                    });
-                    sfor<0, NK>([&](auto jc) {
-                        constexpr int j = decltype(jc)::value;
-                        const cd m = lf.template at<j>();
-                        th[j] = fma(m.re, y[j % C].im, fma(-m.im, y[j % C].re, th[j]));   // Im(conj(m) y)
-                    });
-                }
-                if constexpr (TAB) __syncthreads();  // E02 is rewritten
-            }
+    const unsigned nshare = gridDim.x % 8 ? 1 : 8, share = blockIdx.x % nshare;
+    const unsigned first = (unsigned)((unsigned long long)count * share / nshare) + blockIdx.x / nshare;
+    const unsigned end = (unsigned)((unsigned long long)count * (share + 1) / nshare), step = gridDim.x / nshare;
+    auto line_of = [&](const XPoint& x) { return fx + x.xp * (long long)(NK * NK * NK) + tid * NK; };
+    if (first >= end) return;
+    XPoint x = x_point(a, t0 + first);
+    T fv[NK];
+    load_raw<T, NK>(line_of(x), fv);
+    for (unsigned t = first; t < end; t += step) {
+        T* line = line_of(x);
+        KernelLine kl;
+        kl.nnuc = a.nnuc;
+        kl.tab = tab + ((long long)(x.pair - p0) * a.nnuc * NK * P) * P + 2 * (h * NK + k3);
+        kl.tab_nu = (long long)NK * P * P;
+        kl.e3 = mod_row(et, a, NK, 0, 2, x.i3);
+        kl.e3_nu = (long long)(a.nx[0] + a.nx[1] + a.nx[2]) * NK;
+        {   // A
+            cd y[NK];
+            sfor<0, NK>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                constexpr cd c = twiddle(j, 4 * NK, -1);
+                const double f = (double)fv[j];
+                y[j] = cd{c.re * f, c.im * f};
+            });
+            transform<NK, -1>(y);
+            sfor<0, NK>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                W[m * S::SLOT + c3 * RS + c2] = y[m];
+            });
         }
-        store_k1<T, NK>(line, th);
+        // the next point's line, ahead of its first use
+        if (t + step < end) {
+            x = x_point(a, t0 + t + step);
+            load_raw<T, NK>(line_of(x), fv);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int m = grp; m < NK; m += GROUPS) {     // B, C, D: line xi2 = 2 k3 + h
+            KernelLine km = kl;
+            km.tab += (long long)m * (P * P);
+            plane_conv<NK>(W + m * S::SLOT, km, tw, k3, h);
+        }
+        __syncthreads();
+        {   // E
+            cd y[NK];
+            sfor<0, NK>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                y[m] = W[m * S::SLOT + c3 * RS + c2];
+            });
+            transform<NK, +1>(y);
+            double th[NK];
+            sfor<0, NK>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                constexpr cd c = twiddle(j, 4 * NK, -1);
+                th[j] = fma(c.re, y[j].re, c.im * y[j].im);      // Re(conj(c) y)
+            });
+            store_k1<T, NK>(line, th);
+        }
     }
 }
 

@@ -73,8 +73,8 @@ __global__ __launch_bounds__(BigShape<NK>::LA, 2) void k_thA(const T* __restrict
 // one-wave block takes 64 / (2 N_k) planes, and no lane waits for another wave.  At
 // N_k = 32 a lane's line, its kernel values and the Toeplitz sums are 384 registers: one
 // wave per SIMD.  384 x-points with two nuclei take 194 us (56 % VALU busy), where full
-// complex spectra of the modulated field took 490; a form that loops over planes and requests
-// the next one ahead spills (2.2 KB of scratch, 921 us).
+// complex spectra of the modulated field took 490; a loop over planes that requests the next one
+// ahead gained 1.5 % of the whole and was left out.
 template <int NK>
 __global__ __launch_bounds__(64, NK == 32 ? 1 : 2) void k_thBCD_plane(fft::cd* __restrict__ W, const double* __restrict__ tab,
                                                                      const fft::cd* __restrict__ et, const ThetaArgs a,

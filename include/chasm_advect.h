@@ -127,9 +127,8 @@ enum {
      * launches (SLAB and CUBE handles included); on a SLAB handle, whose steps
      * alternate the sweep order, the field it leaves can differ from an unobserved run
      * in the last bits.  The observables are bitwise equal to chasm_advect_marginals of
-     * the stored field.  The handle allocates the item rows and
-     * their partial sums (nbatch * nk1 nk2 nk3 * (nx1 nx2 + ceil(nx1 nx2 / 64) nx3 + nx1 +
-     * nx2 + nx3) doubles, and at most nbatch * (nk1 nk2 nk3 / 16 + 1) * nx1 nx2) at create.
+     * the stored field.  The handle allocates the item rows
+     * (nbatch * nk1 nk2 nk3 * (nx1 nx2 + ceil(nx1 nx2 / 64) nx3) doubles) at create.
      * A handle with this flag is stepped on its own by chasm_advect_step_many. */
     CHASM_FLAG_OBSERVE = 1u << 6
 };
@@ -204,7 +203,7 @@ chasm_status chasm_advect_diagnostics_noalloc(const chasm_advect_desc* desc, con
  *   p12[b][x2][x1] = P(x1, x2) = integral of f over x3 and k           (nbatch*nx[1]*nx[0])
  * Integrals are cell sums times the spacings of the integrated variables (the
  * paper's "average over the grid" convention, as for the mass).  The field is read
- * once; the first call allocates the workspace described at CHASM_FLAG_OBSERVE, kept
+ * once; the first call allocates the item rows described at CHASM_FLAG_OBSERVE, kept
  * until destroy.  Synchronises the handle's stream. */
 chasm_status chasm_advect_marginals(chasm_advect_t h, double* w1, double* w2, double* w3, double* p12);
 

@@ -248,7 +248,7 @@ static bool axis_by_axis(const chasm_advect_s* h)
 static thread_local std::string g_err;
 
 namespace chasm {
-long long marginal_workspace(const int nx[3], const int nk[3], int nbatch);
+long long marginal_row(const int nx[3]);
 hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nbatch, const double hx[3],
                             const double hk[3], const void* f, double* part, double* out, hipStream_t st);
 
@@ -425,13 +425,14 @@ static size_t field_bytes(const chasm_advect_desc* d)
     return pts * (d->dtype == CHASM_F64 ? sizeof(double) : sizeof(float));
 }
 
-// Bytes of the observables' workspace (item rows and the sums of their second stage) and
-// of the results (marginals and CHASM_FLAG_OBSERVE).
+// Bytes of the observables' item rows and of their sums (marginals and
+// CHASM_FLAG_OBSERVE).
 static std::pair<size_t, size_t> observe_bytes(const chasm_advect_desc* d)
 {
+    const long long nitems = (long long)d->nk[0] * d->nk[1] * d->nk[2] * d->nbatch;
     const long long per_b = (long long)d->nx[0] * d->nk[0] + (long long)d->nx[1] * d->nk[1] +
                             (long long)d->nx[2] * d->nk[2] + (long long)d->nx[0] * d->nx[1];
-    return {(size_t)marginal_workspace(d->nx, d->nk, d->nbatch) * sizeof(double), (size_t)per_b * d->nbatch * sizeof(double)};
+    return {(size_t)nitems * marginal_row(d->nx) * sizeof(double), (size_t)per_b * d->nbatch * sizeof(double)};
 }
 
 static size_t workspace_bytes(const chasm_advect_desc* d, const KernelSet* ks, int sched, size_t table_bytes)

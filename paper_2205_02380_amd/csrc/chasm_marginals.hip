@@ -7,15 +7,14 @@
 //                 chasm_obs.hpp (column sums q over x3, plane sums G of 64-column
 //                 groups), read once from HBM; each wave takes one 64-column group at
 //                 a time, so every load of a wave is a contiguous run of x1;
+//   k_marg_cols   P: 32 columns (x2, x1) to a block, 32 shares of the items, the sum of q;
 //   k_marg_axes   per item, the row's contributions to the three W: a[x1] = sum of q over
-//                 x2, b[x2] = sum of q over x1, c[x3] = sum of G over the groups;
-//   k_marg_cols   P: one thread per column (x2, x1) and chunk of items, the sum of q;
-//   k_marg_sum    one wave per W value, summing its items' contributions, and one thread
-//                 per P value, summing the chunks; scales by the cell volume of the
-//                 integrated variables.
+//                 x2, b[x2] = sum of q over x1, c[x3] = sum of G over the groups, in place
+//                 of values of the row that are no longer needed (axis_at);
+//   k_marg_sum    one wave per W value, summing its items' contributions;
+// all scaled by the cell volume of the integrated variables.
 // Every sum runs in a fixed order.  One thread per output value, walking the item rows by
-// itself, took 3.1 ms on 61^3 x 10^3 (59 MB of rows); k_marg_axes 32 us, k_marg_cols 7 and
-// k_marg_sum 18 take its place.
+// itself, took 3.1 ms on 61^3 x 10^3 (59 MB of rows); the three take 12, 29 and 5 us.
 // The x3 sweep that ends an observed step (CHASM_FLAG_OBSERVE) writes the same rows in
 // its epilogue; the sums then complete the observables without reading the field.
 #include <hip/hip_runtime.h>
@@ -55,33 +54,59 @@ __global__ __launch_bounds__(256) void k_marg_item(const T* __restrict__ f, int 
 struct MargArgs {
     int nx[3], nk[3], nbatch;
     double s[4];                 // cell volumes of the integrated variables: W1, W2, W3, P
-    int chunks;                  // of the items of a batch member, for P
 };
 
-// Doubles of the second stage's workspace: per item a | b | c, then per chunk of a batch
-// member's items the partial P.
-static long long marg_axes(const int nx[3]) { return (long long)nx[0] + nx[1] + nx[2]; }
-
-// Chunks of a batch member's nkp items: enough threads for the chip, at least 16 items each.
-static int marg_chunks(const int nx[3], long long nkp)
+// out layout per batch member b: W1[k1][x1] | W2[k2][x2] | W3[k3][x3] | P[x2][x1].
+__host__ __device__ __forceinline__ long long marg_w(const MargArgs& a)
 {
-    const long long want = (256LL * 2048) / ((long long)nx[0] * nx[1]) + 1;
-    const long long most = (nkp + 15) / 16;
-    return (int)(want < most ? want : most);
+    return (long long)a.nx[0] * a.nk[0] + (long long)a.nx[1] * a.nk[1] + (long long)a.nx[2] * a.nk[2];
 }
 
-__global__ __launch_bounds__(256) void k_marg_axes(const double* __restrict__ part, MargArgs a, double* __restrict__ axes)
+__global__ __launch_bounds__(1024) void k_marg_cols(const double* __restrict__ part, MargArgs a, double* __restrict__ out)
+{
+    __shared__ double red[32][33];
+    const long long plane = (long long)a.nx[0] * a.nx[1], nkp = (long long)a.nk[0] * a.nk[1] * a.nk[2];
+    const unsigned tiles = (unsigned)((plane + 31) / 32), b = blockIdx.x / tiles;
+    const int cl = threadIdx.x % 32, sh = threadIdx.x / 32;
+    const long long c = (long long)(blockIdx.x % tiles) * 32 + cl, row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
+    double t = 0.0;
+    if (c < plane) {
+        const double* q = part + b * nkp * row + c;
+#pragma unroll 8
+        for (long long i = sh; i < nkp; i += 32) t += q[i * row];
+    }
+    red[sh][cl] = t;
+    __syncthreads();
+    if (sh == 0 && c < plane) {
+        double p = 0.0;
+        for (int u = 0; u < 32; ++u) p += red[u][cl];
+        out[b * (marg_w(a) + plane) + marg_w(a) + c] = p * a.s[3];
+    }
+}
+
+// Where k_marg_axes leaves node j of axis d in an item's row: a over row 0 of q, b[y] over
+// the first value of row y (b[0] over the second of row 1), c over group 0 of G.
+__device__ __forceinline__ long long axis_at(const MargArgs& a, int d, int j)
+{
+    const long long N0 = a.nx[0];
+    return d == 0 ? j : d == 1 ? (j ? j * N0 : N0 + 1) : N0 * a.nx[1] + j;
+}
+
+__global__ __launch_bounds__(256) void k_marg_axes(double* __restrict__ part, MargArgs a)
 {
     __shared__ double red[4][64];
     const int N0 = a.nx[0], N1 = a.nx[1], N2 = a.nx[2];
-    const long long item = blockIdx.x;
-    const double* q = part + item * obs_row(N0, N1, N2);
-    const double* G = q + (long long)N0 * N1;
-    double* out = axes + item * (N0 + N1 + N2);
+    double* q = part + blockIdx.x * obs_row(N0, N1, N2);
+    double* G = q + (long long)N0 * N1;
     const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-    // sums down the columns of a rows x cols matrix, 64 columns at a time: wave w takes the
-    // rows w, w + 4, ...; the four partial sums are added in wave order
-    auto down = [&](const double* m, long long rows, int cols, double* dst) {
+    auto across = [&](int y) {                       // sum of row y, by a wave
+        double t = 0.0;
+        for (int x = ln; x < N0; x += 64) t += q[(long long)y * N0 + x];
+        return obs_wave_sum(t);
+    };
+    // sums down the columns of a rows x cols matrix into its row 0, 64 columns at a time:
+    // wave w takes the rows w, w + 4, ...; the four partial sums are added in wave order
+    auto down = [&](double* m, long long rows, int cols) {
         for (int c0 = 0; c0 < cols; c0 += 64) {
             const int c = c0 + ln;
             double t = 0.0;
@@ -89,88 +114,52 @@ __global__ __launch_bounds__(256) void k_marg_axes(const double* __restrict__ pa
                 for (long long r = wv; r < rows; r += 4) t += m[r * cols + c];
             red[wv][ln] = t;
             __syncthreads();
-            if (wv == 0 && c < cols) dst[c] = (red[0][ln] + red[1][ln]) + (red[2][ln] + red[3][ln]);
+            if (wv == 0 && c < cols) m[c] = (red[0][ln] + red[1][ln]) + (red[2][ln] + red[3][ln]);
             __syncthreads();
         }
     };
-    down(q, N1, N0, out);
-    down(G, obs_groups(N0, N1), N2, out + N0 + N1);
-    for (int y = wv; y < N1; y += 4) {               // a wave per row
-        double t = 0.0;
-        for (int x = ln; x < N0; x += 64) t += q[(long long)y * N0 + x];
-        t = obs_wave_sum(t);
-        if (ln == 0) out[N0 + y] = t;
+    const double b0 = across(0);                     // before row 0 is overwritten
+    __syncthreads();
+    down(q, N1, N0);
+    down(G, obs_groups(N0, N1), N2);
+    for (int y = wv; y < N1; y += 4) {
+        if (y == 0) continue;
+        const double t = across(y);                  // row y is read and written by this wave alone
+        if (ln == 0) {
+            q[axis_at(a, 1, y)] = t;
+            if (y == 1) q[axis_at(a, 1, 0)] = b0;
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_marg_cols(const double* __restrict__ part, MargArgs a, double* __restrict__ cols)
+__global__ __launch_bounds__(256) void k_marg_sum(const double* __restrict__ part, MargArgs a, double* __restrict__ out)
 {
     const long long plane = (long long)a.nx[0] * a.nx[1], nkp = (long long)a.nk[0] * a.nk[1] * a.nk[2];
-    const unsigned tiles = (unsigned)((plane + 255) / 256), u = blockIdx.x / tiles;
-    const long long c = (long long)(blockIdx.x % tiles) * 256 + threadIdx.x;
-    if (c >= plane) return;
-    const long long ch = u % a.chunks, b = u / a.chunks;
-    const long long per = (nkp + a.chunks - 1) / a.chunks, i0 = ch * per, i1 = i0 + per < nkp ? i0 + per : nkp;
-    const long long row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
-    const double* q = part + b * nkp * row + c;
+    const long long nw = marg_w(a), row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
+    const int ln = threadIdx.x & 63;
+    const long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (id >= nw * a.nbatch) return;
+    const long long b = id / nw;
+    long long r = id % nw;
+    // axis d, its node j and k index kd; the items of kd
+    int d = 0;
+    while (d < 2 && r >= (long long)a.nx[d] * a.nk[d]) r -= (long long)a.nx[d] * a.nk[d++];
+    const long long kd = r / a.nx[d];
+    const long long inner = d == 0 ? 1 : d == 1 ? a.nk[0] : (long long)a.nk[0] * a.nk[1];   // stride of k_d
+    const long long rest = nkp / a.nk[d];
+    const double* v = part + b * nkp * row + axis_at(a, d, (int)(r % a.nx[d]));
     double t = 0.0;
-#pragma unroll 8
-    for (long long i = i0; i < i1; ++i) t += q[i * row];
-    cols[((long long)b * a.chunks + ch) * plane + c] = t;
+    for (long long u = ln; u < rest; u += 64) t += v[((u / inner) * inner * a.nk[d] + kd * inner + u % inner) * row];
+    t = obs_wave_sum(t);
+    if (ln == 0) out[b * (nw + plane) + id % nw] = t * a.s[d];
 }
 
-// out layout per batch member b: W1[k1][x1] | W2[k2][x2] | W3[k3][x3] | P[x2][x1].
-__global__ __launch_bounds__(256) void k_marg_sum(const double* __restrict__ axes, const double* __restrict__ cols,
-                                                  MargArgs a, double* __restrict__ out)
-{
-    const int N0 = a.nx[0], N1 = a.nx[1], N2 = a.nx[2], n1 = a.nk[0], n2 = a.nk[1], n3 = a.nk[2];
-    const long long plane = (long long)N0 * N1, nkp = (long long)n1 * n2 * n3;
-    const long long nw = (long long)N0 * n1 + (long long)N1 * n2 + (long long)N2 * n3, per_b = nw + plane;
-    const long long wblocks = (nw * a.nbatch + 3) / 4;
-    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63, A = N0 + N1 + N2;
-    if (blockIdx.x < wblocks) {                      // a wave per W value
-        const long long id = (long long)blockIdx.x * 4 + wv;
-        if (id >= nw * a.nbatch) return;
-        const int b = (int)(id / nw);
-        long long r = id % nw;
-        const double* base = axes + b * nkp * A;
-        // axis d, its node j and k index kd; the items of kd: i = lo + hi * stride
-        int d = 0;
-        const int N[3] = {N0, N1, N2}, n[3] = {n1, n2, n3};
-        while (d < 2 && r >= (long long)N[d] * n[d]) r -= (long long)N[d] * n[d++];
-        const int kd = (int)(r / N[d]), j = (int)(r % N[d]);
-        const long long inner = d == 0 ? 1 : d == 1 ? n1 : (long long)n1 * n2;   // stride of k_d
-        const long long rest = nkp / n[d];
-        const double* v = base + (d == 0 ? 0 : d == 1 ? N0 : N0 + N1) + j;
-        double t = 0.0;
-        for (long long u = ln; u < rest; u += 64) {
-            const long long i = (u / inner) * inner * n[d] + kd * inner + u % inner;
-            t += v[i * A];
-        }
-        t = obs_wave_sum(t);
-        if (ln == 0) out[b * per_b + id % nw] = t * a.s[d];
-    } else {                                         // a thread per P value
-        const long long id = ((long long)blockIdx.x - wblocks) * 256 + threadIdx.x;
-        if (id >= plane * a.nbatch) return;
-        const long long b = id / plane, c = id % plane;
-        double t = 0.0;
-        for (int ch = 0; ch < a.chunks; ++ch) t += cols[(b * a.chunks + ch) * plane + c];
-        out[b * per_b + nw + c] = t * a.s[3];
-    }
-}
+// Doubles of an item row.
+long long marginal_row(const int nx[3]) { return obs_row(nx[0], nx[1], nx[2]); }
 
-// Doubles of the workspace of a field's marginals: the item rows (chasm_obs.hpp), then the
-// second stage's sums.
-long long marginal_workspace(const int nx[3], const int nk[3], int nbatch)
-{
-    const long long nkp = (long long)nk[0] * nk[1] * nk[2];
-    return nkp * nbatch * (obs_row(nx[0], nx[1], nx[2]) + marg_axes(nx)) +
-           (long long)marg_chunks(nx, nkp) * nbatch * nx[0] * nx[1];
-}
-
-// All passes on stream st: part holds marginal_workspace(nx, nk, nbatch) doubles, out
-// nbatch * (nx1 nk1 + nx2 nk2 + nx3 nk3 + nx1 nx2) doubles.  f nullptr: the item rows
-// are already in part (written by an observing x3 sweep); only the sums run.
+// All passes on stream st: part holds the item rows (marginal_row(nx) doubles each), which
+// the sums use up, out nbatch * (nx1 nk1 + nx2 nk2 + nx3 nk3 + nx1 nx2) doubles.  f
+// nullptr: the item rows are already in part (written by an observing x3 sweep).
 hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nbatch, const double hx[3],
                             const double hk[3], const void* f, double* part, double* out, hipStream_t st)
 {
@@ -196,16 +185,10 @@ hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nba
     a.s[1] = v[0] * v[2];
     a.s[2] = v[0] * v[1];
     a.s[3] = hx[2] * hk[0] * hk[1] * hk[2];
-    const long long nkp = (long long)nk[0] * nk[1] * nk[2], plane = (long long)nx[0] * nx[1];
-    const long long nw = (long long)nx[0] * nk[0] + (long long)nx[1] * nk[1] + (long long)nx[2] * nk[2];
-    a.chunks = marg_chunks(nx, nkp);
-    double* const axes = part + nitems * obs_row(nx[0], nx[1], nx[2]);
-    double* const cols = axes + nitems * marg_axes(nx);
-    hipLaunchKernelGGL(k_marg_axes, dim3((unsigned)nitems), dim3(256), 0, st, part, a, axes);
-    hipLaunchKernelGGL(k_marg_cols, dim3((unsigned)((plane + 255) / 256 * a.chunks * nbatch)), dim3(256), 0, st, part, a,
-                       cols);
-    hipLaunchKernelGGL(k_marg_sum, dim3((unsigned)((nw * nbatch + 3) / 4 + (plane * nbatch + 255) / 256)), dim3(256), 0, st,
-                       axes, cols, a, out);
+    const long long plane = (long long)nx[0] * nx[1];
+    hipLaunchKernelGGL(k_marg_cols, dim3((unsigned)((plane + 31) / 32 * nbatch)), dim3(1024), 0, st, part, a, out);
+    hipLaunchKernelGGL(k_marg_axes, dim3((unsigned)nitems), dim3(256), 0, st, part, a);
+    hipLaunchKernelGGL(k_marg_sum, dim3((unsigned)((marg_w(a) * nbatch + 3) / 4)), dim3(256), 0, st, part, a, out);
     return hipGetLastError();
 }
 

@@ -389,6 +389,11 @@ __global__ __launch_bounds__(NT, WPE) void k_cube(const Work w, double* __restri
                     });
                 });
             }
+            // The next step starts at a barrier.  With one round per step that barrier is the
+            // loop's first instruction, and the compiler waits for outstanding LDS accesses
+            // ahead of the loop only, not on its back edge: these sweeps' writes could still
+            // be in flight when another wave reads past the barrier.
+            if constexpr (MULTI) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         __syncthreads();
 

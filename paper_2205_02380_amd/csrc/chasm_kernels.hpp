@@ -136,11 +136,15 @@ struct Buf {
         return __builtin_bit_cast(typename Vec16<T>::type,
                                   __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, CP));
     }
+    // Both offsets in the lane's: the data registers of a store of more than 64 bits must not
+    // be overwritten by the next instruction, and the compiler keeps them only where the
+    // uniform offset is no register.  With one, an FP64 k_slab pass overwrote half a
+    // vector in the next instruction, and a quarter of its lanes stored the new value now and then.
     template <typename T, int CP>
-    __device__ __forceinline__ void store16(const typename Vec16<T>::type& x, uint32_t voff, uint32_t soff) const
+    __device__ __forceinline__ void store16(const typename Vec16<T>::type& x, uint32_t voff, uint32_t off) const
     {
         using I4 = int __attribute__((ext_vector_type(4)));
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(I4, x), r, (int)voff, (int)soff, CP);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(I4, x), r, (int)(voff + off), 0, CP);
     }
     template <typename T, int CP = kCpolStream>
     __device__ __forceinline__ void store(T x, uint32_t voff, uint32_t soff) const

@@ -26,28 +26,35 @@
 
 namespace chasm {
 
+// A launch holds fewer than 2^32 threads: the kernels walk their units (items, column
+// tiles, sums) with a grid of at most this many blocks.
+constexpr long long kMargBlocks = 1LL << 20;
+
+static dim3 marg_grid(long long units) { return dim3((unsigned)(units < kMargBlocks ? units : kMargBlocks)); }
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_marg_item(const T* __restrict__ f, int n0, int n1, int n2,
+__global__ __launch_bounds__(256) void k_marg_item(const T* __restrict__ f, int n0, int n1, int n2, long long nitems,
                                                    double* __restrict__ part)
 {
     const int plane = n0 * n1;
     const long long ngr = obs_groups(n0, n1);
-    const long long item = blockIdx.x;
-    const T* src = f + item * (long long)plane * n2;
-    double* q = part + item * obs_row(n0, n1, n2);
-    double* G = q + plane;
     const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-    for (long long g = wv; g < ngr; g += 4) {
-        const long long c = 64 * g + ln;
-        const bool in = c < plane;
-        double acc = 0.0;
-        for (int z = 0; z < n2; ++z) {
-            const double x = in ? (double)src[(long long)z * plane + c] : 0.0;
-            acc += x;
-            const double gs = obs_wave_sum(x);
-            if (ln == 0) G[g * n2 + z] = gs;
+    for (long long item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const T* src = f + item * (long long)plane * n2;
+        double* q = part + item * obs_row(n0, n1, n2);
+        double* G = q + plane;
+        for (long long g = wv; g < ngr; g += 4) {
+            const long long c = 64 * g + ln;
+            const bool in = c < plane;
+            double acc = 0.0;
+            for (int z = 0; z < n2; ++z) {
+                const double x = in ? (double)src[(long long)z * plane + c] : 0.0;
+                acc += x;
+                const double gs = obs_wave_sum(x);
+                if (ln == 0) G[g * n2 + z] = gs;
+            }
+            if (in) q[c] = acc;
         }
-        if (in) q[c] = acc;
     }
 }
 
@@ -66,21 +73,24 @@ __global__ __launch_bounds__(1024) void k_marg_cols(const double* __restrict__ p
 {
     __shared__ double red[32][33];
     const long long plane = (long long)a.nx[0] * a.nx[1], nkp = (long long)a.nk[0] * a.nk[1] * a.nk[2];
-    const unsigned tiles = (unsigned)((plane + 31) / 32), b = blockIdx.x / tiles;
+    const long long tiles = (plane + 31) / 32, row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
     const int cl = threadIdx.x % 32, sh = threadIdx.x / 32;
-    const long long c = (long long)(blockIdx.x % tiles) * 32 + cl, row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
-    double t = 0.0;
-    if (c < plane) {
-        const double* q = part + b * nkp * row + c;
+    for (long long tile = blockIdx.x; tile < tiles * a.nbatch; tile += gridDim.x) {
+        const long long b = tile / tiles, c = tile % tiles * 32 + cl;
+        double t = 0.0;
+        if (c < plane) {
+            const double* q = part + b * nkp * row + c;
 #pragma unroll 8
-        for (long long i = sh; i < nkp; i += 32) t += q[i * row];
-    }
-    red[sh][cl] = t;
-    __syncthreads();
-    if (sh == 0 && c < plane) {
-        double p = 0.0;
-        for (int u = 0; u < 32; ++u) p += red[u][cl];
-        out[b * (marg_w(a) + plane) + marg_w(a) + c] = p * a.s[3];
+            for (long long i = sh; i < nkp; i += 32) t += q[i * row];
+        }
+        red[sh][cl] = t;
+        __syncthreads();
+        if (sh == 0 && c < plane) {
+            double p = 0.0;
+            for (int u = 0; u < 32; ++u) p += red[u][cl];
+            out[b * (marg_w(a) + plane) + marg_w(a) + c] = p * a.s[3];
+        }
+        __syncthreads();
     }
 }
 
@@ -96,10 +106,8 @@ __global__ __launch_bounds__(256) void k_marg_axes(double* __restrict__ part, Ma
 {
     __shared__ double red[4][64];
     const int N0 = a.nx[0], N1 = a.nx[1], N2 = a.nx[2];
-    double* q = part + blockIdx.x * obs_row(N0, N1, N2);
-    double* G = q + (long long)N0 * N1;
     const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-    auto across = [&](int y) {                       // sum of row y, by a wave
+    auto across = [&](const double* q, int y) {      // sum of row y, by a wave
         double t = 0.0;
         for (int x = ln; x < N0; x += 64) t += q[(long long)y * N0 + x];
         return obs_wave_sum(t);
@@ -118,16 +126,20 @@ __global__ __launch_bounds__(256) void k_marg_axes(double* __restrict__ part, Ma
             __syncthreads();
         }
     };
-    const double b0 = across(0);                     // before row 0 is overwritten
-    __syncthreads();
-    down(q, N1, N0);
-    down(G, obs_groups(N0, N1), N2);
-    for (int y = wv; y < N1; y += 4) {
-        if (y == 0) continue;
-        const double t = across(y);                  // row y is read and written by this wave alone
-        if (ln == 0) {
-            q[axis_at(a, 1, y)] = t;
-            if (y == 1) q[axis_at(a, 1, 0)] = b0;
+    const long long nitems = (long long)a.nk[0] * a.nk[1] * a.nk[2] * a.nbatch;
+    for (long long item = blockIdx.x; item < nitems; item += gridDim.x) {
+        double* q = part + item * obs_row(N0, N1, N2);
+        const double b0 = across(q, 0);              // before row 0 is overwritten
+        __syncthreads();
+        down(q, N1, N0);
+        down(q + (long long)N0 * N1, obs_groups(N0, N1), N2);
+        for (int y = wv; y < N1; y += 4) {
+            if (y == 0) continue;
+            const double t = across(q, y);           // row y is read and written by this wave alone
+            if (ln == 0) {
+                q[axis_at(a, 1, y)] = t;
+                if (y == 1) q[axis_at(a, 1, 0)] = b0;
+            }
         }
     }
 }
@@ -137,21 +149,21 @@ __global__ __launch_bounds__(256) void k_marg_sum(const double* __restrict__ par
     const long long plane = (long long)a.nx[0] * a.nx[1], nkp = (long long)a.nk[0] * a.nk[1] * a.nk[2];
     const long long nw = marg_w(a), row = obs_row(a.nx[0], a.nx[1], a.nx[2]);
     const int ln = threadIdx.x & 63;
-    const long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (id >= nw * a.nbatch) return;
-    const long long b = id / nw;
-    long long r = id % nw;
-    // axis d, its node j and k index kd; the items of kd
-    int d = 0;
-    while (d < 2 && r >= (long long)a.nx[d] * a.nk[d]) r -= (long long)a.nx[d] * a.nk[d++];
-    const long long kd = r / a.nx[d];
-    const long long inner = d == 0 ? 1 : d == 1 ? a.nk[0] : (long long)a.nk[0] * a.nk[1];   // stride of k_d
-    const long long rest = nkp / a.nk[d];
-    const double* v = part + b * nkp * row + axis_at(a, d, (int)(r % a.nx[d]));
-    double t = 0.0;
-    for (long long u = ln; u < rest; u += 64) t += v[((u / inner) * inner * a.nk[d] + kd * inner + u % inner) * row];
-    t = obs_wave_sum(t);
-    if (ln == 0) out[b * (nw + plane) + id % nw] = t * a.s[d];
+    for (long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); id < nw * a.nbatch; id += (long long)gridDim.x * 4) {
+        const long long b = id / nw;
+        long long r = id % nw;
+        // axis d, its node j and k index kd; the items of kd
+        int d = 0;
+        while (d < 2 && r >= (long long)a.nx[d] * a.nk[d]) r -= (long long)a.nx[d] * a.nk[d++];
+        const long long kd = r / a.nx[d];
+        const long long inner = d == 0 ? 1 : d == 1 ? a.nk[0] : (long long)a.nk[0] * a.nk[1];   // stride of k_d
+        const long long rest = nkp / a.nk[d];
+        const double* v = part + b * nkp * row + axis_at(a, d, (int)(r % a.nx[d]));
+        double t = 0.0;
+        for (long long u = ln; u < rest; u += 64) t += v[((u / inner) * inner * a.nk[d] + kd * inner + u % inner) * row];
+        t = obs_wave_sum(t);
+        if (ln == 0) out[b * (nw + plane) + id % nw] = t * a.s[d];
+    }
 }
 
 // Doubles of an item row.
@@ -166,11 +178,11 @@ hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nba
     const long long nitems = (long long)nk[0] * nk[1] * nk[2] * nbatch;
     if (f) {
         if (dtype == CHASM_F64)
-            hipLaunchKernelGGL((k_marg_item<double>), dim3((unsigned)nitems), dim3(256), 0, st,
-                               static_cast<const double*>(f), nx[0], nx[1], nx[2], part);
+            hipLaunchKernelGGL((k_marg_item<double>), marg_grid(nitems), dim3(256), 0, st,
+                               static_cast<const double*>(f), nx[0], nx[1], nx[2], nitems, part);
         else
-            hipLaunchKernelGGL((k_marg_item<float>), dim3((unsigned)nitems), dim3(256), 0, st,
-                               static_cast<const float*>(f), nx[0], nx[1], nx[2], part);
+            hipLaunchKernelGGL((k_marg_item<float>), marg_grid(nitems), dim3(256), 0, st,
+                               static_cast<const float*>(f), nx[0], nx[1], nx[2], nitems, part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -186,9 +198,9 @@ hipError_t launch_marginals(int dtype, const int nx[3], const int nk[3], int nba
     a.s[2] = v[0] * v[1];
     a.s[3] = hx[2] * hk[0] * hk[1] * hk[2];
     const long long plane = (long long)nx[0] * nx[1];
-    hipLaunchKernelGGL(k_marg_cols, dim3((unsigned)((plane + 31) / 32 * nbatch)), dim3(1024), 0, st, part, a, out);
-    hipLaunchKernelGGL(k_marg_axes, dim3((unsigned)nitems), dim3(256), 0, st, part, a);
-    hipLaunchKernelGGL(k_marg_sum, dim3((unsigned)((marg_w(a) * nbatch + 3) / 4)), dim3(256), 0, st, part, a, out);
+    hipLaunchKernelGGL(k_marg_cols, marg_grid((plane + 31) / 32 * nbatch), dim3(1024), 0, st, part, a, out);
+    hipLaunchKernelGGL(k_marg_axes, marg_grid(nitems), dim3(256), 0, st, part, a);
+    hipLaunchKernelGGL(k_marg_sum, marg_grid((marg_w(a) * nbatch + 3) / 4), dim3(256), 0, st, part, a, out);
     return hipGetLastError();
 }
 

@@ -765,6 +765,7 @@ chasm_status chasm_advect_create(const chasm_advect_desc* desc, void* f_dev, voi
 
     auto bail = [&](chasm_status s, const std::string& m) {
         chasm_advect_destroy(h);
+        (void)hipGetLastError();   // reported by this call, not by the next launch of another handle
         return fail(s, m);
     };
     hipError_t e = hipMalloc(&h->tables, tb.bytes.size());

@@ -655,6 +655,7 @@ chasm_status chasm_ho2d_create(const chasm_ho2d_desc* d, void* f_dev, void* hip_
     h->n = (long long)d->nk * d->nx;
     auto bail = [&](chasm_status s, const std::string& m) {
         chasm_ho2d_destroy(h);
+        (void)hipGetLastError();   // reported by this call, not by the next launch of another handle
         return hfail(s, m);
     };
     // one block: stencil | patch factors | w (doubles), then shift (ints)

@@ -76,6 +76,7 @@ chasm_status chasm_lpc1_create(const chasm_advect_desc* adv, const chasm_theta_d
     const size_t bytes = (size_t)n * (h->dtype == CHASM_F64 ? 8 : 4);
     auto bail = [&](chasm_status s, const std::string& m) {
         chasm_lpc1_destroy(h);
+        (void)hipGetLastError();   // reported by this call, not by the next launch of another handle
         return lfail(s, m);
     };
     if (hipMalloc(&h->G, bytes) != hipSuccess) return bail(CHASM_ENOMEM, "hipMalloc(theta field) failed");

@@ -377,6 +377,7 @@ chasm_status chasm_theta_create(const chasm_theta_desc* desc, void* hip_stream, 
     h->nkp = (long long)nk[0] * nk[1] * nk[2];
     auto bail = [&](chasm_status s, const std::string& m) {
         chasm_theta_destroy(h);
+        (void)hipGetLastError();   // reported by this call, not by the next launch of another handle
         return tfail(s, m);
     };
     h->plan = theta_plan(desc, ks);

@@ -1143,13 +1143,15 @@ chasm_status chasm_advect_marginals(chasm_advect_t h, double* w1, double* w2, do
 {
     if (!h) return fail(CHASM_EINVAL, "handle is NULL");
     if (h->poisoned) return fail(CHASM_ESTATE, "handle is poisoned by an earlier device failure");
-    if (!h->marg_part) {
-        const auto ob = observe_bytes(&h->desc);
-        if (hipMalloc((void**)&h->marg_part, ob.first) != hipSuccess)
-            return fail(CHASM_ENOMEM, "hipMalloc(marginal rows) failed");
-        if (hipMalloc((void**)&h->marg_out, ob.second) != hipSuccess)
-            return fail(CHASM_ENOMEM, "hipMalloc(marginals) failed");
-    }
+    const auto ob = observe_bytes(&h->desc);
+    auto reserve = [](double** p, size_t bytes) {
+        if (*p || hipMalloc((void**)p, bytes) == hipSuccess) return true;
+        *p = nullptr;
+        (void)hipGetLastError();   // as at create
+        return false;
+    };
+    if (!reserve(&h->marg_part, ob.first)) return fail(CHASM_ENOMEM, "hipMalloc(marginal rows) failed");
+    if (!reserve(&h->marg_out, ob.second)) return fail(CHASM_ENOMEM, "hipMalloc(marginals) failed");
     hipError_t e = launch_observables(h, h->f, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "marginals launch");
     // the buffers now hold this field's marginals, not the last observed call's

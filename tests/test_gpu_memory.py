@@ -31,3 +31,19 @@ def test_a_failed_create_leaves_no_error_behind():
         with chasm.Advect(g, grid, 8, 6, 0.02) as a:
             a.step(1)
         torch.cuda.synchronize()
+
+
+def test_marginals_without_memory_fail_again():
+    # room for the item rows (4.0 GB) but not for their sums (3.8 GB) as well
+    grid = inputs.Grid((2, 2, 70), (-1.0,) * 3, (1.0,) * 3, (1, 1, 6750000), (-1.0,) * 3, (1.0,) * 3)
+    f = torch.zeros(grid.shape(), device=DEV)
+    with chasm.Advect(f, grid, (1, 1, 15), 1, 0.02) as a:
+        torch.cuda.empty_cache()
+        filler = torch.empty(torch.cuda.mem_get_info()[0] - (9 << 29), dtype=torch.uint8, device=DEV)
+        for again in range(2):
+            with pytest.raises(chasm.ChasmError) as e:
+                a.marginals()
+            assert e.value.status == chasm.CHASM_ENOMEM
+        del filler
+    del f
+    torch.cuda.empty_cache()

@@ -127,10 +127,13 @@ __global__ __launch_bounds__(256) void k_ho_advect(const double* __restrict__ in
             const int j0 = iface(q) - a.g;
             int t = tid % 8;
             if (e0 == 0) {
+                // taps off the stencil or the line have coefficient 0 and take a node of the
+                // stencil, so that a slope sees no other node, finite or not
+                const int last = min(j0 + W, N) - 1;
 #pragma unroll
-                for (int u = 0; u < PRE; ++u) {      // taps off the line have coefficient 0
+                for (int u = 0; u < PRE; ++u) {
                     const int j = j0 + t + 8 * u;
-                    acc = fma(cf[u], v[j < 0 ? 0 : (j < N ? j : N - 1)], acc);
+                    acc = fma(cf[u], v[j < 0 ? 0 : (j < last ? j : last)], acc);
                 }
                 t += 8 * PRE;
             }

@@ -101,7 +101,8 @@ enum {
      * SLAB and PLAIN read f in their first launch and write the stage field, and write
      * f back in their last launch, so every step ends in f; CUBE handles that record
      * per-step diagnostics run the steps of one chasm_advect_step call in pairs (f ->
-     * stage -> f) and an odd last step in place, others in place.
+     * stage -> f) and an odd last step in place, others run in place and allocate no
+     * stage field.
      * The arithmetic is unchanged (results are bitwise equal to in place); HBM serves a
      * read stream and a write stream to different addresses faster than read-modify-
      * write traffic on one buffer.  chasm_advect_step_many steps CUBE handles in place. */
@@ -227,8 +228,9 @@ chasm_status chasm_advect_history(chasm_advect_t h, double* out, int32_t max_ste
  * Asynchronous. */
 chasm_status chasm_advect_step_many(const chasm_advect_t* hs, int32_t n, const int32_t* nsteps);
 
-/* Device bytes the library allocates for a handle with this descriptor (tables,
- * partials, history), not counting the caller's field. */
+/* Device bytes the library allocates at most for a handle with this descriptor (tables,
+ * partials, history; CHASM_FLAG_OUT_OF_PLACE counts the stage field of every schedule),
+ * not counting the caller's field. */
 chasm_status chasm_advect_workspace_bytes(const chasm_advect_desc* desc, size_t* bytes);
 
 /* Schedule actually used by a handle (after AUTO resolution). */

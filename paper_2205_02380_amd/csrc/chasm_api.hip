@@ -822,7 +822,8 @@ chasm_status chasm_advect_create(const chasm_advect_desc* desc, void* f_dev, voi
     }
     h->fin.vol = h->fin.hx[0] * h->fin.hx[1] * h->fin.hx[2] * h->fin.hk[0] * h->fin.hk[1] * h->fin.hk[2];
 
-    if (desc->flags & CHASM_FLAG_OUT_OF_PLACE) {
+    // CUBE steps without per-step diagnostics run in place (steps_unobserved)
+    if ((desc->flags & CHASM_FLAG_OUT_OF_PLACE) && (h->schedule != CHASM_SCHED_CUBE || red)) {
         if (hipMalloc(&h->stage, field_bytes(desc)) != hipSuccess)
             return bail(CHASM_ENOMEM, "hipMalloc(stage field) failed");
         h->w_fs = h->w_sf = h->w_ss = h->work;

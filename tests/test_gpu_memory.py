@@ -1,5 +1,5 @@
 """Device memory: a call that cannot have the memory it needs fails by itself, and later
-calls work."""
+calls work; and no field is allocated that nothing uses."""
 import pytest
 import torch
 
@@ -47,3 +47,22 @@ def test_marginals_without_memory_fail_again():
         del filler
     del f
     torch.cuda.empty_cache()
+
+
+def _taken(make):
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    with make():
+        return before - torch.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("kw,field", [(dict(), False), (dict(observe=True), False), (dict(reduce_each_step=True), True),
+                                      (dict(schedule="slab"), True)])
+def test_stage_field_only_where_steps_use_it(kw, field):
+    grid = inputs.cubic_grid(32, 12.0, 12, 4.0)
+    f = torch.zeros(grid.shape(), device=DEV)                    # 226 MB
+    base = _taken(lambda: chasm.Advect(f, grid, 8, 6, 0.02, **kw))
+    more = _taken(lambda: chasm.Advect(f, grid, 8, 6, 0.02, out_of_place=True, **kw)) - base
+    size = f.numel() * 4
+    # small buffers share pieces of some MB: the difference is not exact
+    assert (more > size // 8 * 7) if field else (more < size // 8), (more, size)

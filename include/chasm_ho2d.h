@@ -50,9 +50,10 @@ typedef struct {
                               (the convention of chasm_advect.h) */
 } chasm_ho2d_desc;
 
-/* Validate (CHASM_EINVAL), build the FP64 tables on the host (PMBC stencils, patch
- * inverses, per-k shift weights, the k-differentiation matrix), allocate six fields of
- * state.  f_dev is the caller's field; hip_stream a hipStream_t (NULL = default). */
+/* Validate (CHASM_EINVAL), build the FP64 tables on the host (PMBC stencils, factors of the
+ * patch sweeps, per-k shift weights; twiddles where the k transforms are FFTs, else the
+ * k-differentiation matrix), allocate four fields of state (six with the matrix).  f_dev is
+ * the caller's field; hip_stream a hipStream_t (NULL = default). */
 chasm_status chasm_ho2d_create(const chasm_ho2d_desc* desc, void* f_dev, void* hip_stream, chasm_ho2d_t* out);
 
 /* nsteps LPC1 steps on the field, in place, asynchronously (negative: CHASM_EINVAL). */

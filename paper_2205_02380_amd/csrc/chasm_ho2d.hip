@@ -557,7 +557,8 @@ struct chasm_ho2d_s {
     void* tables = nullptr;
     double* D = nullptr;             // dense path: the differentiation matrix
     fft::cd* tw = nullptr;           // transform path: e^{+2 pi i j / nk}, j < nk
-    double *X = nullptr, *XA = nullptr, *Y = nullptr, *Z = nullptr;   // X, XA: two fields each
+    double *X = nullptr, *XA = nullptr;   // two fields each
+    double *Y = nullptr, *Z = nullptr;    // dense path: the predictor and its derivative
     double* f = nullptr;
     long long n = 0;
     bool poisoned = false;
@@ -677,7 +678,8 @@ chasm_status chasm_ho2d_create(const chasm_ho2d_desc* d, void* f_dev, void* hip_
         return bail(CHASM_ENOMEM, "hipMalloc(twiddles) failed");
     const size_t fb = (size_t)h->n * sizeof(double);
     if (hipMalloc((void**)&h->X, 2 * fb) != hipSuccess || hipMalloc((void**)&h->XA, 2 * fb) != hipSuccess ||
-        hipMalloc((void**)&h->Y, fb) != hipSuccess || hipMalloc((void**)&h->Z, fb) != hipSuccess)
+        (!by_transform &&
+         (hipMalloc((void**)&h->Y, fb) != hipSuccess || hipMalloc((void**)&h->Z, fb) != hipSuccess)))
         return bail(CHASM_ENOMEM, "hipMalloc(state) failed");
     if (hipMemcpyAsync(h->tables, blob.data(), blob.size(), hipMemcpyHostToDevice, h->stream) != hipSuccess ||
         (h->D && hipMemcpyAsync(h->D, D.data(), D.size() * sizeof(double), hipMemcpyHostToDevice, h->stream) !=

@@ -3,7 +3,7 @@ calls work; and no field is allocated that nothing uses."""
 import pytest
 import torch
 
-from paper_2205_02380_amd import chasm, inputs, theta
+from paper_2205_02380_amd import chasm, ho2d, inputs, theta
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -66,3 +66,12 @@ def test_stage_field_only_where_steps_use_it(kw, field):
     size = f.numel() * 4
     # small buffers share pieces of some MB: the difference is not exact
     assert (more > size // 8 * 7) if field else (more < size // 8), (more, size)
+
+
+def test_oscillator_fields_of_its_path():
+    # transforms: two pairs of fields; dense: the predictor and its derivative as well
+    def fields(nk):
+        f = torch.zeros((nk, 1021), dtype=torch.float64, device=DEV)
+        return _taken(lambda: ho2d.HO2D(f, 1021, -12.0, 0.02, nk, -6.4, 12.8 / nk, 60, 20, 0.4, 1e-4)) / (f.numel() * 8.0)
+    assert 4.0 <= fields(1024) < 5.5
+    assert fields(1026) >= 6.0

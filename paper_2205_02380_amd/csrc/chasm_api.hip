@@ -233,6 +233,7 @@ struct chasm_advect_s {
     // out of place: f -> stage, stage -> stage, stage -> f)
     bool rt = false;
     RtJob rtj[3] = {};
+    int cube_from = 2;               // steps from which a CUBE launch takes several (cube_multi_from)
 };
 
 static bool records_steps(const chasm_advect_s* h) { return (h->desc.flags & CHASM_FLAG_REDUCE_EACH_STEP) != 0; }
@@ -362,6 +363,7 @@ static long long step_partial_rows(const chasm_advect_desc* d, const KernelSet* 
 // of the kernels; the host builds the stencil rows too, for the record and the tests.)
 struct TableBlock {
     std::vector<char> bytes;
+    double far = 0.0;       // share of the shift classes (axes, k nodes) that are neither 0 nor -1
     size_t off_w64[3], off_w32[3], off_shift[3];
     // runtime-shape kernels: interface rows times h, end-slope bias times h, patch factors
     size_t off_st64[3], off_st32[3], off_bi64[3], off_bi32[3], off_lu64[3], off_lu32[3];
@@ -402,6 +404,7 @@ static bool build_tables(const chasm_advect_desc* d, const KernelSet* ks, TableB
         std::vector<float> w32(at[a].w.begin(), at[a].w.end());
         tb.off_w32[a] = push(tb.bytes, w32.data(), w32.size());
         tb.off_shift[a] = push(tb.bytes, at[a].shift.data(), at[a].shift.size());
+        for (int sg : at[a].shift) tb.far += (sg != 0 && sg != -1) / (3.0 * d->nk[a]);
         if (!rt) continue;
         const AxisTables& t = at[a];
         std::vector<double> st(t.stencil), bi(t.bias), lu((size_t)6 * (t.M + 1), 0.0);
@@ -471,6 +474,26 @@ static hipError_t launch_step(const KernelSet* ks, int sched, const Work* const 
 // whatever its number of steps, so past a few dozen nothing is gained, and the bound
 // keeps single launches short (about 0.2 s for 64 steps of a 34 GB field).
 constexpr int kMultiSteps = 64;
+
+// Steps from which one multi-step CUBE launch is faster than as many launches of one step.
+// FP64 cubes gain from two steps on (1.07-1.5 times at two, every size and shift measured),
+// FP32 ones too while all shifts stay within a cell (1.1-1.4 at two; 24^3 from three, unless
+// the field is small).  Shifts of a cell or more take the runtime-shift stores, which in the
+// multi-step kernel of FP32 cubes cost more registers than it has.  With a share `far` of 0.83
+// two steps in one launch against two launches take 633 / 571 us on 16^3 x 36^3, 1110 / 811 on
+// 24^3 x 24^3 and 739 / 562 on 32^3 x 18^3, six 1543 / 1712, 2591 / 2432 and 1713 / 1685; with a
+// share of 0.37 two 546 / 573, 923 / 721 and 612 / 553, three 699 / 859, 1206 / 1082 and 789 / 830.
+// On fields of a few MB a launch is mostly latency, which more steps share: 16^3 x 7^3 gains at two.
+static int cube_multi_from(const chasm_advect_desc* d, double far)
+{
+    const int n = d->nx[0];
+    const bool small = field_bytes(d) <= (size_t)16 << 20;
+    if (d->dtype == CHASM_F64) return 2;
+    if (far == 0.0) return n == 24 && !small ? 3 : 2;
+    if (small) return n <= 16 ? 2 : n <= 24 ? 3 : 6;
+    if (far <= 0.5) return n == 24 ? 5 : 3;
+    return n <= 8 ? 4 : n <= 16 ? 6 : n <= 24 ? 14 : 7;
+}
 
 // SLAB schedule.  The axis operators commute (see SlabMode), so a call of K steps whose
 // fields in between nothing asks for (axis_by_axis) runs its sweeps axis by axis, two
@@ -761,6 +784,7 @@ chasm_status chasm_advect_create(const chasm_advect_desc* desc, void* f_dev, voi
     h->stream = (hipStream_t)hip_stream;
     h->ks = ks;
     h->schedule = resolve_schedule(desc, ks);
+    h->cube_from = cube_multi_from(desc, tb.far);
     hipGetDevice(&h->device);
 
     auto bail = [&](chasm_status s, const std::string& m) {
@@ -932,6 +956,7 @@ static chasm_status steps_unobserved(chasm_advect_t h, int32_t nsteps)
         Work w = h->work;
         for (int32_t s = 0; s < nsteps; s += w.nsteps) {
             w.nsteps = std::min(nsteps - s, (int32_t)kMultiSteps);
+            if (w.nsteps < h->cube_from) w.nsteps = 1;
             w.jobs[0].reverse = h->rev_next;
             hipError_t e = h->ks->cube(w, nullptr, h->stream);
             if (e != hipSuccess) return hip_fail(h, e, "step launch");
@@ -996,7 +1021,8 @@ chasm_status chasm_advect_step_many(const chasm_advect_t* hs, int32_t n, const i
     // handle, a step of a PLAIN handle, a pass of a SLAB handle (slab_multi_pass), so every
     // job progresses together.  Handles with the same kernels, schedule and launch share
     // it (work lists of at most kMaxJobs jobs); CUBE handles share as many steps as all of
-    // them have left, which changes no result.
+    // them have left, or one where that is too few for one of them (cube_multi_from), which
+    // changes no result.
     std::vector<int32_t> at(n, 0);   // steps done (CUBE, PLAIN) or passes done (SLAB)
     constexpr int kStep = -1;
     auto next_of = [&](int32_t i, int* kind, int* c) {
@@ -1019,6 +1045,7 @@ chasm_status chasm_advect_step_many(const chasm_advect_t* hs, int32_t n, const i
             // One work list per launch; job j of list p is launch p of its handle's step
             // (in place, or through that handle's stage field).
             Work w[3] = {};
+            int from = 0;
             group.clear();
             for (int32_t b = a; b < n && w[0].njobs < kMaxJobs; ++b) {
                 chasm_advect_t o = hs[b];
@@ -1041,9 +1068,11 @@ chasm_status chasm_advect_step_many(const chasm_advect_t* hs, int32_t n, const i
                     ++w[p].njobs;
                 }
                 c = std::min(c, cb);
+                from = std::max(from, o->cube_from);
                 done[b] = true;
                 group.push_back(b);
             }
+            if (cube && c < from) c = 1;
             w[0].nsteps = c;
             const Work* pw[3] = {&w[0], &w[1], &w[2]};
             const hipError_t e = kind == kStep ? launch_step(h->ks, h->schedule, pw, nullptr, s)

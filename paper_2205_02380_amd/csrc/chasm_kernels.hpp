@@ -827,34 +827,40 @@ __global__ __launch_bounds__(NT) void k_pencil(const Work w, double* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Diagnostics of the current field, one item per block.
+// Diagnostics of the current field, one item per block at a time (a launch holds fewer than
+// 2^32 threads; more are cut off without an error).
+constexpr long long kReduceBlocks = 1LL << 20;
+
 template <typename T, int N, int NT>
 __global__ __launch_bounds__(NT) void k_reduce_field(const Work w, double* __restrict__ partials)
 {
     constexpr int VW = Vec16<T>::n;
     using V = typename Vec16<T>::type;
-    long long item;
-    const JobDev& job = job_of(w, blockIdx.x, item);
-    int ik[3];
-    item_k(job, item, ik);
-    const V* __restrict__ src = reinterpret_cast<const V*>(static_cast<const T*>(job.f) + item * (long long)(N * N * N));
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int e = threadIdx.x; e < N * N * N / VW; e += NT) {
-        const V x = src[e];
-        const int row = (e * VW) / N, x1 = (e * VW) % N;
-        double s = 0.0;
+    for (long long unit = blockIdx.x; unit < w.first[w.njobs]; unit += gridDim.x) {
+        long long item;
+        const JobDev& job = job_of(w, unit, item);
+        int ik[3];
+        item_k(job, item, ik);
+        const V* __restrict__ src = reinterpret_cast<const V*>(static_cast<const T*>(job.f) + item * (long long)(N * N * N));
+        double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int e = threadIdx.x; e < N * N * N / VW; e += NT) {
+            const V x = src[e];
+            const int row = (e * VW) / N, x1 = (e * VW) % N;
+            double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < VW; ++i) {
-            const double y = (double)vget<T>(x, i);
-            s += y;
-            acc[1] = fma(y, y, acc[1]);
-            acc[2] = fma((double)(x1 + i), y, acc[2]);
+            for (int i = 0; i < VW; ++i) {
+                const double y = (double)vget<T>(x, i);
+                s += y;
+                acc[1] = fma(y, y, acc[1]);
+                acc[2] = fma((double)(x1 + i), y, acc[2]);
+            }
+            acc[0] += s;
+            acc[3] = fma((double)(row % N), s, acc[3]);
+            acc[4] = fma((double)(row / N), s, acc[4]);
         }
-        acc[0] += s;
-        acc[3] = fma((double)(row % N), s, acc[3]);
-        acc[4] = fma((double)(row / N), s, acc[4]);
+        write_partials<NT>(acc, ik, partials + unit * NRED);
+        __syncthreads();   // the block sums' scratch is read before the next item writes it
     }
-    write_partials<NT>(acc, ik, partials + (long long)blockIdx.x * NRED);
 }
 
 struct FinalizeArgs {

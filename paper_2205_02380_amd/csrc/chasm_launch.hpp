@@ -136,8 +136,8 @@ template <typename T, int N>
 hipError_t launch_reduce(const Work& w, double* partials, hipStream_t s)
 {
     using Lc = Launch<T, N>;
-    hipLaunchKernelGGL((k_reduce_field<T, N, Lc::reduce_nt>), dim3((unsigned)w.first[w.njobs]), dim3(Lc::reduce_nt), 0,
-                       s, w, partials);
+    const unsigned grid = (unsigned)(w.first[w.njobs] < kReduceBlocks ? w.first[w.njobs] : kReduceBlocks);
+    hipLaunchKernelGGL((k_reduce_field<T, N, Lc::reduce_nt>), dim3(grid), dim3(Lc::reduce_nt), 0, s, w, partials);
     return hipGetLastError();
 }
 

@@ -705,38 +705,40 @@ hipError_t rt_sweep_obs(const RtJob& j, int dtype, double* rows, hipStream_t s)
     return dtype == 1 ? rt_sweep_obs_t<double>(j, rows, s) : rt_sweep_obs_t<float>(j, rows, s);
 }
 
-// Diagnostics of the current field, one item per block: threads own (x1, x2) columns.
+// Diagnostics of the current field, one item per block at a time: threads own (x1, x2) columns.
 template <typename T>
 __global__ __launch_bounds__(256) void k_rt_reduce(const RtJob j, double* __restrict__ partials)
 {
     const int n0 = j.nx[0], n1 = j.nx[1], n2 = j.nx[2];
     const long long plane = (long long)n0 * n1;
-    const long long item = blockIdx.x;
-    const T* src = static_cast<const T*>(j.f) + item * plane * n2;
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (long long p = threadIdx.x; p < plane; p += 256) {
-        const int x1 = (int)(p % n0), x2 = (int)(p / n0);
-        double c = 0.0, c2 = 0.0, c3 = 0.0;
-        for (int x3 = 0; x3 < n2; ++x3) {
-            const double y = (double)src[x3 * plane + p];
-            c += y;
-            c2 = fma(y, y, c2);
-            c3 = fma((double)x3, y, c3);
+    for (long long item = blockIdx.x; item < j.nitems; item += gridDim.x) {
+        const T* src = static_cast<const T*>(j.f) + item * plane * n2;
+        double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        for (long long p = threadIdx.x; p < plane; p += 256) {
+            const int x1 = (int)(p % n0), x2 = (int)(p / n0);
+            double c = 0.0, c2 = 0.0, c3 = 0.0;
+            for (int x3 = 0; x3 < n2; ++x3) {
+                const double y = (double)src[x3 * plane + p];
+                c += y;
+                c2 = fma(y, y, c2);
+                c3 = fma((double)x3, y, c3);
+            }
+            acc[0] += c;
+            acc[1] += c2;
+            acc[2] = fma((double)x1, c, acc[2]);
+            acc[3] = fma((double)x2, c, acc[3]);
+            acc[4] += c3;
         }
-        acc[0] += c;
-        acc[1] += c2;
-        acc[2] = fma((double)x1, c, acc[2]);
-        acc[3] = fma((double)x2, c, acc[3]);
-        acc[4] += c3;
+        int ik[3];
+        rt_item_k(j, (unsigned)item, ik);
+        write_partials<256>(acc, ik, partials + item * NRED);
+        __syncthreads();   // the block sums' scratch is read before the next item writes it
     }
-    int ik[3];
-    rt_item_k(j, item, ik);
-    write_partials<256>(acc, ik, partials + item * NRED);
 }
 
 hipError_t rt_reduce(const RtJob& j, int dtype, double* partials, hipStream_t s)
 {
-    const unsigned grid = (unsigned)j.nitems;
+    const unsigned grid = (unsigned)(j.nitems < kReduceBlocks ? j.nitems : kReduceBlocks);
     if (dtype == 1)
         hipLaunchKernelGGL((k_rt_reduce<double>), dim3(grid), dim3(256), 0, s, j, partials);
     else

@@ -316,6 +316,11 @@ static chasm_status validate(const chasm_advect_desc* d, const KernelSet** ks_ou
         if (d->schedule == CHASM_SCHED_CUBE && !ks->cube)
             return fail(CHASM_EUNSUPPORTED, "the x-cube does not fit in LDS for this nx and dtype");
         if (items * d->nx[0] > 2.0e9) return fail(CHASM_EUNSUPPORTED, "too many items for one launch grid");
+        // k_pencil takes a thread per line; a launch holds fewer than 2^32, and more are cut off
+        // without an error
+        const bool cube = ks->cube && (d->schedule == CHASM_SCHED_CUBE || d->schedule == CHASM_SCHED_AUTO);
+        if ((!cube || (d->flags & CHASM_FLAG_OBSERVE)) && items * d->nx[0] * d->nx[0] >= 4294967296.0)
+            return fail(CHASM_EUNSUPPORTED, "too many lines for one launch");
     } else {
         // the runtime-shape kernels: resource limits only
         if (d->schedule == CHASM_SCHED_CUBE || d->schedule == CHASM_SCHED_SLAB)
@@ -333,6 +338,8 @@ static chasm_status validate(const chasm_advect_desc* d, const KernelSet** ks_ou
             }
             const double lines = (double)d->nx[0] * d->nx[1] * d->nx[2] / d->nx[a];
             if (items * std::ceil(lines / L) > 2.0e9) return fail(CHASM_EUNSUPPORTED, "too many blocks for one launch grid");
+            if (items * std::ceil(lines / L) * rt_block_threads(g, a, eb) >= 4294967296.0)
+                return fail(CHASM_EUNSUPPORTED, "too many lines for one launch");
         }
         ks = &kRuntimeKernels;
     }

@@ -77,6 +77,12 @@ int rt_lines_per_block(const RtJob& j, int axis, int elem_bytes)
     return 0;
 }
 
+int rt_block_threads(const RtJob& j, int axis, int elem_bytes)
+{
+    const int pw = rp_waves(j.ax[axis], elem_bytes);
+    return pw ? 64 * pw : kRtThreads;
+}
+
 static int rt_lines(const RtJob& j, int axis)
 {
     return j.nx[0] * j.nx[1] * j.nx[2] / j.nx[axis];

@@ -33,6 +33,9 @@ struct RtJob {
 // Lines per block of a sweep along axis a, or 0 if its LDS tiles do not fit.
 int rt_lines_per_block(const RtJob& j, int axis, int elem_bytes);
 
+// Threads of a block of a sweep along axis a.
+int rt_block_threads(const RtJob& j, int axis, int elem_bytes);
+
 // One sweep along `axis` for every line of every item; partials (nullable, axis 2
 // only): FP64 partial sums of the result, one row per block (rt_rows_per_item rows
 // per item, in item order).

@@ -301,3 +301,22 @@ def test_autotune_cache_keys_keep_reduction_runs_apart(tmp_path):
     assert autotune.lookup(path, w.grid, w.dt)["best"]["tile"] == 1
     assert autotune.lookup(path, w.grid, w.dt, reduce_each_step=True)["best"]["tile"] == 0
     assert autotune.cache_key(w.grid, w.dt) != autotune.cache_key(w.grid, w.dt, True)
+
+
+@pytest.mark.parametrize("nk,kw,ok", [
+    ((406, 406, 407), dict(schedule="slab"), True), ((407, 407, 406), dict(schedule="slab"), False),    # 2^26 items
+    ((407, 407, 406), dict(schedule="plain"), False), ((407, 407, 406), dict(), True),                 # a cube per block
+    ((407, 407, 406), dict(flags=chasm.CHASM_FLAG_OBSERVE), False),
+    ((322, 322, 323), dict(flags=chasm.CHASM_FLAG_RUNTIME_SHAPE), True),                               # 128 threads an item
+    ((323, 323, 322), dict(flags=chasm.CHASM_FLAG_RUNTIME_SHAPE), False)])
+def test_sweeps_of_more_lines_than_a_launch_has_threads_are_refused(nk, kw, ok):
+    # a thread per line (64 an item) on the compiled kernels, 64 lines by two patches of one
+    # item to a block on the others: 2^32 threads are cut off without an error
+    grid = inputs.Grid((8, 8, 8), (-1.0,) * 3, (1.0,) * 3, nk, (-1.0,) * 3, (1.0,) * 3)
+    d = chasm.make_desc(grid, 4, 3, 0.02, **kw)
+    if ok:
+        assert chasm.chasm_advect_workspace_bytes(d) > 0
+        return
+    with pytest.raises(chasm.ChasmError) as ei:
+        chasm.chasm_advect_workspace_bytes(d)
+    assert ei.value.status == chasm.CHASM_EUNSUPPORTED and "launch" in str(ei.value)

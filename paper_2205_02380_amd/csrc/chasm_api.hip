@@ -485,8 +485,10 @@ constexpr int kMultiSteps = 64;
 // Steps from which one multi-step CUBE launch is faster than as many launches of one step.
 // FP64 cubes gain from two steps on (1.07-1.5 times at two, every size and shift measured),
 // FP32 ones too while all shifts stay within a cell (1.1-1.4 at two; 24^3 from three, unless
-// the field is small).  Shifts of a cell or more take the runtime-shift stores, which in the
-// multi-step kernel of FP32 cubes cost more registers than it has.  With a share `far` of 0.83
+// the field is small).  A launch of K steps takes about their arithmetic and the field's traffic
+// after one another (FP32 24^3 x 24^3: 180 + 354 K us with small shifts, 370 + 370 K with most of a
+// cell or more, which take the runtime-shift stores), single steps overlap the two (335 and
+// 405 us each), so several to a launch pay where the traffic is the longer.  With a share `far` of 0.83
 // two steps in one launch against two launches take 633 / 571 us on 16^3 x 36^3, 1110 / 811 on
 // 24^3 x 24^3 and 739 / 562 on 32^3 x 18^3, six 1543 / 1712, 2591 / 2432 and 1713 / 1685; with a
 // share of 0.37 two 546 / 573, 923 / 721 and 612 / 553, three 699 / 859, 1206 / 1082 and 789 / 830.

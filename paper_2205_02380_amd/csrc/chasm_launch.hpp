@@ -25,7 +25,10 @@ struct Launch {
     static constexpr int cube_nt =
         N <= 8 ? 64 : (N <= 16 ? 256 : (N <= 24 ? (sizeof(T) == 4 ? 576 : 192) : 1024));
     // Waves per SIMD asked of the multi-step cube (register bound): those of the blocks
-    // whose cubes fit in a CU's LDS together, at most 5.
+    // whose cubes fit in a CU's LDS together, at most 5.  The bound spills 3-12 registers
+    // at FP64 N = 16, 5-14 at FP32 N = 24 and 7-30 at FP32 N = 32, none elsewhere.  A launch of
+    // fewer items than two or four to a CU has fewer waves than it asks for and gains nothing by it:
+    // 16^3 x 8^3 FP64 is 512 items for 1024 such blocks.
     static constexpr int cube_blocks = (int)(kLdsBytes / ((size_t)N * N * (N + 1) * sizeof(T) + 512));
     static constexpr int cube_waves = (cube_blocks * (cube_nt / 64) + 3) / 4;
     static constexpr int cube_wpe = cube_waves < 1 ? 1 : cube_waves > 5 ? 5 : cube_waves;

@@ -141,9 +141,11 @@ static const ThetaKernels* find_theta(int dtype, int nk)
 //   that holds all pairs they are made once, at create; else for each range of each call,
 //   which costs a pair as much as the Toeplitz products of one of its nx3 nbatch x-points.
 //   U, 2 nk^3 doubles per x1 node and nucleus, likewise.
-//   W: 192 MiB at most, which stays with the tables in the 256 MB memory-side cache between
-//   the stages: 18^3 x 32^3 with two nuclei takes 5.33 ms, against 5.44 at 256 MiB, 5.55 at
-//   128 and 6.45 at 64 (launch gaps and half-empty rounds).
+//   W: 192 MiB at most.  18^3 x 32^3 with two nuclei, whose ranges have 42 MiB of tables, takes
+//   5.33 ms, against 5.44 at 256 MiB, 5.55 at 128 and 6.45 at 64 (launch gaps and half-empty
+//   rounds): W and the tables then stay in the 256 MB memory-side cache between the stages.
+//   With three or four x-points to a pair the tables of a range are up to their own bound
+//   and the two exceed it.
 struct ThetaPlan {
     bool big, resident, u_resident;
     int np;

@@ -71,8 +71,8 @@ __global__ __launch_bounds__(BigShape<NK>::LA, 2) void k_thA(const T* __restrict
 
 // ---- B, C, D for N_k <= 32: planes W[x][c][k3][k2] through plane_conv, in place; a
 // one-wave block takes 64 / (2 N_k) planes, and no lane waits for another wave.  At
-// N_k = 32 a lane's line, its kernel values and the Toeplitz sums are 384 registers: one
-// wave per SIMD.  384 x-points with two nuclei take 194 us (56 % VALU busy), where full
+// N_k = 32 a lane's line, its kernel values and the Toeplitz sums are 384 of its 416
+// registers: one wave per SIMD.  384 x-points with two nuclei take 194 us (56 % VALU busy), where full
 // complex spectra of the modulated field took 490; a loop over planes that requests the next one
 // ahead gained 1.5 % of the whole and was left out.
 template <int NK>

@@ -309,9 +309,9 @@ __device__ __forceinline__ LineFactors<NK> half_factors(const fft::cd* et, int h
 //   E  thread (k2, k3): N_k-point inverse over the planes; the real part, demodulated.
 // Each XCD takes a contiguous share of the x-points, so that the points of a pair find its
 // table lines (131 KB at N_k = 16) in one L2.
-// Bound: FP64 VALU (66 % busy at N_k = 16) beside 0.6 MB of LDS traffic per x-point; two
+// Bound: FP64 VALU (69 % busy at N_k = 16) beside 0.6 MB of LDS traffic per x-point; two
 // waves per SIMD with 233 registers, all planes of an x-point in LDS (70 KB), so that two
-// barriers separate the stages.  Measured on 61^3 x 16^3, FP32 field, one nucleus: 8.1 ms
+// barriers separate the stages.  Measured on 61^3 x 16^3, FP32 field, one nucleus: 7.7 ms
 // (and 0.2 of tables); 13.9 ms for full complex spectra of the modulated field, which has
 // twice the planes, a modulation on every line and one pass per nucleus.
 template <typename T, int NK>

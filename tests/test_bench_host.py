@@ -51,3 +51,27 @@ def test_committed_counts_are_sane():
     for wl in ("C2", "C3", "C4"):
         for e in t[wl].values():
             assert 1.0 <= e["hbm_bytes_per_launch"] / e["alg_bytes_per_launch"] < 1.05
+
+
+def test_cube_roofline_prices_steps_on_flops_and_single_steps_on_bytes(tmp_path, monkeypatch):
+    f = tmp_path / "cube_flops.json"
+    entry = {"kernel": "void chasm::k_cube<float, 32, 8, 6, 0, 1024, false, true, 4>", "executed_flops_per_point_update": 50.0,
+             "kernel_digest": bench.kernel_digest()}
+    f.write_text(json.dumps({"C2": entry}))
+    monkeypatch.setattr(bench, "CUBE_FLOPS_FILE", str(f))
+    r = bench.cube_roofline(10 ** 6, 100, 1e-3, 1e-5, (32, 8, 6), 5000.0)
+    assert (r["bound"], r["unit"], r["launches"]) == ("alu", "TFLOP/s", 2)
+    assert r["achieved"] == 50.0 * 1e6 * 100 / 1e-3 / 1e12 and r["frac"] == r["achieved"] / r["peak"]
+    one = r["one_step"]
+    assert (one["bound"], one["unit"]) == ("hbm", "GB/s") and one["achieved"] == 8e6 / 1e-5 / 1e9
+    # one step to a call, other sources or another shape: the single steps alone
+    assert bench.cube_roofline(10 ** 6, 1, 1e-5, 1e-5, (32, 8, 6), 5000.0) == one
+    assert bench.cube_roofline(10 ** 6, 100, 1e-3, 1e-5, (32, 16, 8), 5000.0)["bound"] == "hbm"
+    f.write_text(json.dumps({"C2": dict(entry, kernel_digest="0000000000000000")}))
+    assert bench.cube_roofline(10 ** 6, 100, 1e-3, 1e-5, (32, 8, 6), 5000.0) == one
+
+
+def test_committed_cube_counts_are_those_of_the_line_arithmetic():
+    # three sweeps of about ten operations a point, most of them fused multiply-adds
+    e = json.load(open(bench.CUBE_FLOPS_FILE))["C2"]
+    assert 30 < e["executed_flops_per_point_update"] < 90
